@@ -109,7 +109,10 @@ typedef struct {
                                      shapes and precision (saved activations):
                                      skip re-encoding.  Without the flag X and
                                      Y are rebuilt from the records
-                                     (activation checkpointing). */
+                                     (activation checkpointing), as they are
+                                     with it where the FP64 form ran on 0/1
+                                     planes (both relations without values,
+                                     with unique cells). */
 
 /* Status block read back by tcu_sync_status (host copy). */
 typedef struct {

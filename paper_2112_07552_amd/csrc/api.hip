@@ -265,6 +265,20 @@ hipError_t encode_one(const tcu_relation &R, int which, int rows, int cols, doub
     return launch_encode_zeroed(R, which, rows, cols, Z, st, which, sc.p, sc.bytes, s);
 }
 
+// The FP64 form over relations with unique cells and no values: both
+// encodings are 0/1, and the product runs on int8 planes (count.hip), which
+// take the places of X and Y in the workspace.  The planes pad lines to 128
+// and keys to 32, so a tiny matrix may not have room for them; such a product
+// stays on the FP64 matrix cores.
+bool counts_form(const tcu_relation *A, const tcu_relation *B, int32_t M, int32_t K, int32_t N,
+                 tcu_precision p) {
+    if (p != TCU_PREC_FP64 || A->val != nullptr || B->val != nullptr) return false;
+    if (!(A->flags & TCU_REL_UNIQUE_CELLS) || !(B->flags & TCU_REL_UNIQUE_CELLS)) return false;
+    if (M > (1 << 30) || N > (1 << 30)) return false;  // padded line counts stay int
+    return count_plane_bytes(M, K) <= (size_t)M * (size_t)K * sizeof(double) &&
+           count_plane_bytes(N, K) <= (size_t)K * (size_t)N * sizeof(double);
+}
+
 // X (M x K) and Y (K x N) from the records; `count_only` encodes ones.
 hipError_t encode_both(const tcu_relation &A, const tcu_relation &B, int32_t M, int32_t K,
                        int32_t N, double *X, double *Y, StatusBlock *st, bool count_only,
@@ -761,6 +775,9 @@ tcu_status tcu::join_agg_fwd_ws(const tcu_relation *A, const tcu_relation *B, in
     const EncScratch sc = enc_scratch(ws, ws_bytes, L, A, B, M, K, N);
 
     TCU_TRY(launch_clear_status(st, stream));
+    if (counts_form(A, B, M, K, N, p))
+        return hip_status(launch_count(*A, *B, M, K, N, at<int8_t>(ws, L.x), at<int8_t>(ws, L.y),
+                                       st, C, count, stream));
     if (planes) {
         // exact pair counts, Section 3.1's 0/1 encodings (unique cells): one
         // int8 product with exact int32 sums (K < 2^31)
@@ -827,7 +844,9 @@ tcu_status tcu_join_agg_bwd(const tcu_relation *A, const tcu_relation *B, int32_
     const EncScratch sc = enc_scratch(ws, ws_bytes, L, A, B, M, K, N);
 
     if (dA_val == nullptr && dB_val == nullptr) return TCU_OK;
-    const bool saved = (flags & TCU_BWD_SAVED_ENCODINGS) != 0;
+    // the 0/1 product on int8 planes leaves no X and Y behind
+    const bool saved =
+        (flags & TCU_BWD_SAVED_ENCODINGS) != 0 && !counts_form(A, B, M, K, N, p);
     // With both gradients, the gather of dA (memory-bound) and, when the
     // encodings are rebuilt, the encoding of X run on a second stream beside
     // the matrix products on the caller's stream:

@@ -166,6 +166,17 @@ hipError_t launch_gemm_f64_split(int trans_a, int trans_b, int m, int n, int k, 
 // or the product fills at most one round.
 int gemm_f64_row_cut(int m, int n);
 
+// count.hip: the product of two 0/1 encodings (relations with unique cells,
+// values ignored) on int8 planes, as doubles into C and / or int32 into cnt
+// (either may be NULL; both M x N, row stride N).  qa and qb hold
+// count_plane_bytes(M, K) and count_plane_bytes(N, K) bytes, 16-byte aligned.
+// Records outside the shape are counted in st (NULL: not counted).  M and N
+// at most 2^30.
+size_t count_plane_bytes(int64_t lines, int64_t len);
+hipError_t launch_count(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                        int8_t *qa, int8_t *qb, StatusBlock *st, double *C, int32_t *cnt,
+                        hipStream_t s);
+
 // dict.hip: dictionary encoding (ranks in the sorted union of two columns).
 size_t dict_workspace_bytes(int64_t n);
 hipError_t run_dict_encode(const long long *a, int64_t n_a, const long long *b, int64_t n_b,
