@@ -27,13 +27,18 @@
 //  * Tiles are numbered so that each of the 8 XCDs (workgroup w runs on XCD
 //    w mod 8) owns a contiguous run of tiles, grouped 8 tile-rows deep, so
 //    the A and B panels a run needs stay in that XCD's L2.
-//  * Whole-tile launches (the common case: m, n >= 128, k >= 16, 16-byte
-//    aligned operands; edge tiles are moved back inside the matrix and a
-//    partial last stage of k is added by a second, guarded launch) run a
-//    main loop whose address arithmetic is all scalar (see the whole-tile
-//    path below): busy matrix cores leave vector-ALU instructions few issue
-//    slots.
+//  * The tile kernel runs products of at least one tile (m, n >= 128, k >=
+//    16); edge tiles are moved back inside the matrix, and the last k % 16
+//    terms come straight from memory.  Its main loop's address arithmetic is
+//    all scalar (see the tile path below): busy matrix cores leave vector-ALU
+//    instructions few issue slots.
+//  * Products whose output has too few 128 x 128 tiles to fill the chip, or
+//    edges that waste much of one, run on the direct kernel (below), whose
+//    tiles are an eighth or a sixteenth of that; pick_kernel holds the rule.
+#include <math.h>
+
 #include <algorithm>
+#include <type_traits>
 
 #include "internal.h"
 
@@ -55,43 +60,6 @@ template <bool KC>
 struct Tile {
     static constexpr int elems = KC ? 128 * KPAD : BK * OPAD;
 };
-
-// Global -> registers: 4 chunks of 2 doubles per thread.
-// KC:  element (o, kk) of the tile is P[(o0 + o) * ld + k0 + kk]
-// !KC: element (o, kk) of the tile is P[(k0 + kk) * ld + o0 + o]
-// `fast` (uniform across the workgroup) says the whole 128 x 16 tile lies
-// inside the operand and 16-byte loads are aligned: then the loads carry no
-// per-element guard, so the compiler emits straight-line dwordx4 loads that
-// stay in flight across the MFMAs of the current stage.  Edge tiles take the
-// guarded path.
-template <bool KC, bool FULL>
-__device__ inline void load_tile(const double *__restrict__ P, int64_t ld, int o0, int k0,
-                                 int oext, int kext, bool vec, double2 (&r)[4]) {
-    const int tid = threadIdx.x;
-    const bool fast = FULL || (vec && o0 + 128 <= oext && k0 + BK <= kext);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid + THREADS * i;
-        int o, kk;
-        if (KC) { o = c >> 3; kk = (c & 7) * 2; }
-        else    { kk = c >> 6; o = (c & 63) * 2; }
-        const int go = o0 + o, gk = k0 + kk;
-        // the two elements of the chunk run along the contiguous index
-        const int64_t base = KC ? (int64_t)go * ld + gk : (int64_t)gk * ld + go;
-        if (fast) {
-            r[i] = *reinterpret_cast<const double2 *>(P + base);
-        } else {
-            const bool in0 = go < oext && gk < kext;
-            const bool in1 = KC ? (go < oext && gk + 1 < kext) : (gk < kext && go + 1 < oext);
-            if (vec && in1) {
-                r[i] = *reinterpret_cast<const double2 *>(P + base);
-            } else {
-                r[i].x = in0 ? P[base] : 0.0;
-                r[i].y = in1 ? P[base + 1] : 0.0;
-            }
-        }
-    }
-}
 
 template <bool KC>
 __device__ inline void store_tile(double *__restrict__ L, const double2 (&r)[4]) {
@@ -119,16 +87,18 @@ __device__ inline void read_frags(const double *__restrict__ L, int wbase, int t
     }
 }
 
-// ----- whole-tile path: no vector-ALU work in the main loop.  While the
-// matrix cores are busy, VALU instructions of every wave on the SIMD get few
-// issue slots, so the whole-tile loop keeps its address arithmetic scalar:
-// each panel load is a uniform SGPR base (advanced by scalar arithmetic) plus
+// ----- tile path: no vector-ALU work in the main loop.  While the matrix
+// cores are busy, VALU instructions of every wave on the SIMD get few issue
+// slots, so the loop keeps its address arithmetic scalar: each panel load is a uniform SGPR base (advanced by scalar arithmetic) plus
 // the lane's fixed 32-bit byte offset, and the loop is unrolled over the two
 // LDS buffers so every LDS access is a fixed register plus an immediate.
 
 typedef __attribute__((address_space(1))) const char gchar;
-typedef double d2v __attribute__((ext_vector_type(2)));
+// 16-byte loads at 8-byte alignment (global memory takes them): leading
+// dimensions, base addresses and moved tiles may be odd
+typedef double d2v __attribute__((ext_vector_type(2), aligned(8)));
 typedef __attribute__((address_space(1))) const d2v gd2v;
+typedef __attribute__((address_space(1))) const double gdbl;
 
 // A uniform global address computed on the vector ALU moved to scalar
 // registers (kept in the global address space, so loads stay global loads).
@@ -181,7 +151,7 @@ __device__ __forceinline__ void load_panel(const Panel &q, int kt, double2 (&r)[
     }
 }
 
-// One stage of the whole-tile loop reading LDS buffer CUR: loads of stage
+// One stage of the tile loop reading LDS buffer CUR: loads of stage
 // kt + 1 (the last stage reloads itself into the idle buffer), 3 k-steps of
 // MFMAs, the loaded tiles stored to buffer CUR ^ 1, the last k-step, a
 // barrier.
@@ -217,7 +187,9 @@ __device__ __forceinline__ void full_stage(int kt, int nk, const Panel &pa, cons
     __syncthreads();
 }
 
-__device__ inline void tile_coords(int tiles_m, int tiles_n, int &tm, int &tn) {
+template <int TILE_M, int TILE_N>
+__device__ inline void tile_coords(int m, int n, int &tm, int &tn) {
+    const int tiles_m = (m + TILE_M - 1) / TILE_M, tiles_n = (n + TILE_N - 1) / TILE_N;
     const int nt = tiles_m * tiles_n;
     const int wg = blockIdx.x;
     const int per = nt / NUM_XCD;
@@ -233,39 +205,26 @@ __device__ inline void tile_coords(int tiles_m, int tiles_n, int &tm, int &tn) {
 
 // A_KC: op(A)'s contraction index is contiguous (trans_a == 0).
 // B_KC: op(B)'s contraction index is contiguous (trans_b == 1).
-// FULL: every tile is whole (edge tiles moved back inside the matrix, k a
-// multiple of 16: the launcher adds a partial last stage separately) and
-// both operands allow 16-byte loads; the loads then carry no guards, and the
-// stores only skip the cells a moved tile shares with its neighbour.
-template <bool A_KC, bool B_KC, bool FULL>
+// Every tile is whole: edge tiles are moved back to end at m (or n), and the
+// stores skip the cells a moved tile shares with its neighbour.
+template <bool A_KC, bool B_KC>
 __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
                 const double *__restrict__ B, int64_t ldb, double *__restrict__ C, int64_t ldc,
-                int vec_a, int vec_b, int accumulate, int kc = 0, int64_t cstride = 0) {
+                int accumulate) {
     __shared__ __attribute__((aligned(16))) double lds_a[2][Tile<A_KC>::elems];
     __shared__ __attribute__((aligned(16))) double lds_b[2][Tile<B_KC>::elems];
 
-    // split contraction (kc > 0): workgroup row y of the grid multiplies the
-    // chunk [y kc, (y + 1) kc) of k into its own partial product at C + y cstride
-    if (kc > 0) {
-        const int k0 = (int)blockIdx.y * kc;
-        A += A_KC ? (int64_t)k0 : (int64_t)k0 * lda;
-        B += B_KC ? (int64_t)k0 : (int64_t)k0 * ldb;
-        C += (int64_t)blockIdx.y * cstride;
-        k = min(kc, k - k0);
-    }
-
-    const int tiles_m = (m + BM - 1) / BM, tiles_n = (n + BN - 1) / BN;
     int tm, tn;
-    tile_coords(tiles_m, tiles_n, tm, tn);
-    // the cells this tile owns start at (rlo, clo); on the whole-tile path a
-    // tile that would run past an edge is moved back to end at m (or n), so
-    // it stays whole and in bounds, and stores only the cells it owns
+    tile_coords<BM, BN>(m, n, tm, tn);
+    // the cells this tile owns start at (rlo, clo)
     const int rlo = tm * BM, clo = tn * BN;
-    const int m0 = FULL ? min(rlo, m - BM) : rlo, n0 = FULL ? min(clo, n - BN) : clo;
+    const int m0 = min(rlo, m - BM), n0 = min(clo, n - BN);
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave & 1, wn = wave >> 1;
+    const int lane = threadIdx.x & 63;
+    const int j = lane >> 4, l16 = lane & 15;
 
     d4 acc[FM][FN];
 #pragma unroll
@@ -273,62 +232,42 @@ gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
 #pragma unroll
         for (int b = 0; b < FN; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
 
-    const int nk = (k + BK - 1) / BK;
-    if constexpr (FULL) {
-        const Panel pa = make_panel<A_KC>(A, lda, m0);
-        const Panel pb = make_panel<B_KC>(B, ldb, n0);
-        {
-            double2 ra[4], rb[4];
-            load_panel(pa, 0, ra);
-            load_panel(pb, 0, rb);
-            store_tile<A_KC>(lds_a[0], ra);
-            store_tile<B_KC>(lds_b[0], rb);
-        }
-        __syncthreads();
-        for (int kt = 0; kt < nk; kt += 2) {
-            full_stage<A_KC, B_KC, 0>(kt, nk, pa, pb, lds_a, lds_b, wm, wn, acc);
-            if (kt + 1 < nk) full_stage<A_KC, B_KC, 1>(kt + 1, nk, pa, pb, lds_a, lds_b, wm, wn, acc);
-        }
-    } else {
-    double2 ra[4], rb[4];
-    load_tile<A_KC, FULL>(A, lda, m0, 0, m, k, vec_a, ra);
-    load_tile<B_KC, FULL>(B, ldb, n0, 0, n, k, vec_b, rb);
-    store_tile<A_KC>(lds_a[0], ra);
-    store_tile<B_KC>(lds_b[0], rb);
+    const int nk = k / BK;  // at least 1
+    const Panel pa = make_panel<A_KC>(A, lda, m0);
+    const Panel pb = make_panel<B_KC>(B, ldb, n0);
+    {
+        double2 ra[4], rb[4];
+        load_panel(pa, 0, ra);
+        load_panel(pb, 0, rb);
+        store_tile<A_KC>(lds_a[0], ra);
+        store_tile<B_KC>(lds_b[0], rb);
+    }
     __syncthreads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int cur = kt & 1;
-        const bool more = kt + 1 < nk;
-        // The last stage reloads its own (in-bounds) tile and stores it to
-        // the idle buffer, which no wave reads any more: loads and stores are
-        // unconditional, so the compiler neither sinks the loads behind the
-        // MFMAs nor keeps the staging registers in scratch.  The scheduling
-        // barrier pins the loads ahead of the stage's MFMAs.
-        const int knext = (more ? kt + 1 : kt) * BK;
-        load_tile<A_KC, FULL>(A, lda, m0, knext, m, k, vec_a, ra);
-        load_tile<B_KC, FULL>(B, ldb, n0, knext, n, k, vec_b, rb);
-        __builtin_amdgcn_sched_barrier(0);
+    for (int kt = 0; kt < nk; kt += 2) {
+        full_stage<A_KC, B_KC, 0>(kt, nk, pa, pb, lds_a, lds_b, wm, wn, acc);
+        if (kt + 1 < nk) full_stage<A_KC, B_KC, 1>(kt + 1, nk, pa, pb, lds_a, lds_b, wm, wn, acc);
+    }
+    // the last k % 16 terms, lane group j's term of step t at k = 4 t + j
+    for (int kk = nk * BK; kk < k; kk += 4) {
+        const int gk = kk + j;
+        double fa[FM], fb[FN];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            double fa[FM], fb[FN];
-            read_frags<A_KC, FM>(lds_a[cur], wm * WM, t, fa);
-            read_frags<B_KC, FN>(lds_b[cur], wn * WN, t, fb);
-#pragma unroll
-            for (int a = 0; a < FM; ++a)
-#pragma unroll
-                for (int b = 0; b < FN; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0,
-                                                                     0);
+        for (int a = 0; a < FM; ++a) {
+            const int64_t o = m0 + wm * WM + a * 16 + l16;
+            fa[a] = gk < k ? A[A_KC ? o * lda + gk : (int64_t)gk * lda + o] : 0.0;
         }
-        store_tile<A_KC>(lds_a[cur ^ 1], ra);
-        store_tile<B_KC>(lds_b[cur ^ 1], rb);
-        __syncthreads();
-    }
+#pragma unroll
+        for (int b = 0; b < FN; ++b) {
+            const int64_t o = n0 + wn * WN + b * 16 + l16;
+            fb[b] = gk < k ? B[B_KC ? o * ldb + gk : (int64_t)gk * ldb + o] : 0.0;
+        }
+#pragma unroll
+        for (int a = 0; a < FM; ++a)
+#pragma unroll
+            for (int b = 0; b < FN; ++b)
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
     }
 
-    const int lane = threadIdx.x & 63;
-    const int j = lane >> 4, l16 = lane & 15;
 #pragma unroll
     for (int a = 0; a < FM; ++a) {
 #pragma unroll
@@ -337,7 +276,7 @@ gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int row = m0 + wm * WM + a * 16 + j + 4 * i;
-                if (FULL ? (row >= rlo && col >= clo) : (row < m && col < n)) {
+                if (row >= rlo && col >= clo) {
                     double *dst = C + (int64_t)row * ldc + col;
                     *dst = accumulate ? *dst + acc[a][b][i] : acc[a][b][i];
                 }
@@ -346,42 +285,302 @@ gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
     }
 }
 
+// ----- direct path: small tiles, fragments straight from memory.  A
+// workgroup's four waves share one tile of 16 TM x 16 TN cells and split the
+// contraction, so a wave needs neither LDS nor barriers until the four partial
+// tiles are added at the end (in wave order: the same result on every run).
+// What bounds it is the latency of its loads: three stages of 16 k are in
+// registers, each stage's loads issued one after every MFMA (64 cycles), since
+// loads issued in one run leave the matrix pipe idle (2048^3 products 262 us
+// against 299 with the loads first).  Any edge and alignment is taken: rows
+// past the end are clamped to the last one and not stored.
+//
+// k within a stage: lane group j's element t is k = 8 (t / 2) + 2 j + t % 2,
+// so a lane of an operand with contiguous k reads 16 bytes and four lanes 64
+// contiguous ones.  An operand with contiguous outer index is read in pairs
+// of blocks: lane l's elements are columns 2 l and 2 l + 1 of the pair's 32,
+// one 16-byte load (tiles at an edge: one 8-byte load per block).
+// WIDE: lane offsets beyond 32 bits (huge leading dimensions).
+template <bool KC, int F, bool WIDE>
+struct DirectOp {
+    gchar *base;  // the tile's first outer index, the wave's first k
+    int64_t ldb;  // bytes between consecutive values of the strided index
+    typename std::conditional<WIDE, uint64_t, uint32_t>::type off[F];
+};
+
+template <bool KC, int F, bool WIDE>
+__device__ __forceinline__ DirectOp<KC, F, WIDE> direct_op(const double *P, int64_t ld, int o0,
+                                                           int ext, int k0) {
+    typedef typename std::conditional<WIDE, uint64_t, uint32_t>::type off_t;
+    const int j = (threadIdx.x & 63) >> 4, l16 = threadIdx.x & 15;
+    DirectOp<KC, F, WIDE> q;
+    q.base = to_sgpr(KC ? P + (int64_t)o0 * ld + k0 : P + (int64_t)k0 * ld + o0);
+    q.ldb = ld * 8;
+#pragma unroll
+    for (int b = 0; b < F; ++b) {
+        const int o = min(KC ? 16 * b + l16 : 32 * (b >> 1) + 2 * l16 + (b & 1), ext - 1 - o0);
+        q.off[b] = KC ? ((off_t)o * (off_t)ld + 2u * j) * 8u : (2u * j * (off_t)ld + (off_t)o) * 8u;
+    }
+    return q;
+}
+
+// Loads per stage of one operand.
+template <bool KC, int F, bool EDGE>
+constexpr int direct_items() { return KC ? 2 * F : (EDGE ? 4 * F : 2 * F); }
+
+// Load I of the stage whose first k is at byte address b.
+template <bool KC, int F, bool EDGE, bool WIDE>
+__device__ __forceinline__ void direct_load(const DirectOp<KC, F, WIDE> &o, gchar *b, int I,
+                                            double (&f)[F][4]) {
+    const int blk = KC ? I >> 1 : (EDGE ? I >> 2 : (I >> 2) * 2);
+    const int t = KC ? 2 * (I & 1) : I & 3;
+    gchar *bi = KC ? b + 32 * t : b + (8 * (t >> 1) + (t & 1)) * o.ldb;
+    auto off = o.off[blk];
+    // a scalar base and a lane offset, as load_panel
+    asm volatile("" : "+s"(bi));
+    asm volatile("" : "+v"(off));
+    if (KC || !EDGE) {
+        const d2v v = *reinterpret_cast<gd2v *>(bi + off);
+        f[blk][t] = v.x;
+        if (KC) f[blk][t + 1] = v.y;
+        else f[blk + 1][t] = v.y;
+    } else {
+        f[blk][t] = *reinterpret_cast<gdbl *>(bi + off);
+    }
+}
+
+// The stages 0 .. S - 1 of 16 k, S >= 1.
+template <bool A_KC, bool B_KC, int TM, int TN, bool EDGE, bool WIDE>
+__device__ __forceinline__ void direct_stages(const DirectOp<A_KC, TM, WIDE> &oa,
+                                              const DirectOp<B_KC, TN, WIDE> &ob, int S,
+                                              d4 (&acc)[TM][TN]) {
+    constexpr int NB = TM * TN > 4 ? 3 : 2;  // stages in registers
+    constexpr int IA = direct_items<A_KC, TM, EDGE>(), IB = direct_items<B_KC, TN, EDGE>();
+    constexpr int MF = 4 * TM * TN;
+    static_assert(IA + IB <= 2 * MF, "at most two loads per MFMA");
+    constexpr int R = (IA + IB + MF - 1) / MF;
+    const int64_t sa = A_KC ? 128 : 16 * oa.ldb, sb = B_KC ? 128 : 16 * ob.ldb;
+    double fa[NB][TM][4], fb[NB][TN][4];
+#pragma unroll
+    for (int u = 0; u < NB - 1; ++u) {
+        gchar *ba = oa.base + min(u, S - 1) * sa, *bb = ob.base + min(u, S - 1) * sb;
+#pragma unroll
+        for (int i = 0; i < IA; ++i) direct_load<A_KC, TM, EDGE, WIDE>(oa, ba, i, fa[u]);
+#pragma unroll
+        for (int i = 0; i < IB; ++i) direct_load<B_KC, TN, EDGE, WIDE>(ob, bb, i, fb[u]);
+    }
+    for (int s = 0; s < S; s += NB) {
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            if (s + u >= S) continue;
+            // the last stages load stage S - 1 again
+            const int nx = min(s + u + NB - 1, S - 1);
+            gchar *ba = oa.base + nx * sa, *bb = ob.base + nx * sb;
+            asm volatile("" : "+s"(ba), "+s"(bb));
+#pragma unroll
+            for (int i = 0; i < MF; ++i) {
+                const int t = i / (TM * TN), a = i % (TM * TN) / TN, b = i % TN;
+                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[u][a][t], fb[u][b][t],
+                                                                 acc[a][b], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const int q = i * R + r;
+                    if (q < IA)
+                        direct_load<A_KC, TM, EDGE, WIDE>(oa, ba, q, fa[(u + NB - 1) % NB]);
+                    else if (q < IA + IB)
+                        direct_load<B_KC, TN, EDGE, WIDE>(ob, bb, q - IA, fb[(u + NB - 1) % NB]);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+}
+
+// The last `left` (1 .. 15) values of k, past them zeros on both sides.
+template <bool KC, int F, bool WIDE>
+__device__ __forceinline__ void direct_tail(const DirectOp<KC, F, WIDE> &o, int S, int left,
+                                            double (&f)[F][4]) {
+    const int j = (threadIdx.x & 63) >> 4;
+    gchar *b = o.base + S * (KC ? (int64_t)128 : 16 * o.ldb);
+#pragma unroll
+    for (int q = 0; q < F; ++q)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int kk = 8 * (t >> 1) + (t & 1);  // plus 2 j, already in the lane's offset
+            double v = 0.0;
+            if (2 * j + kk < left)
+                v = *reinterpret_cast<gdbl *>(b + (KC ? (int64_t)8 * kk : kk * o.ldb) + o.off[q]);
+            f[q][t] = v;
+        }
+}
+
+// kc > 0: split contraction, workgroup row y of the grid multiplies the chunk
+// [y kc, (y + 1) kc) of k into its own partial product at C + y cstride.
+template <bool A_KC, bool B_KC, int TM, int TN, bool WIDE>
+__global__ void __launch_bounds__(THREADS)
+gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
+                   const double *__restrict__ B, int64_t ldb, double *__restrict__ C,
+                   int64_t ldc, int accumulate, int kc, int64_t cstride) {
+    constexpr int TILE_M = 16 * TM, TILE_N = 16 * TN, W = THREADS / 64, E = 4 * TM * TN;
+    static_assert((A_KC || TM % 2 == 0) && (B_KC || TN % 2 == 0), "pairs of blocks");
+    __shared__ double red[W * E * 64];
+    if (kc > 0) {
+        const int c0 = (int)blockIdx.y * kc;
+        A += A_KC ? (int64_t)c0 : (int64_t)c0 * lda;
+        B += B_KC ? (int64_t)c0 : (int64_t)c0 * ldb;
+        C += (int64_t)blockIdx.y * cstride;
+        k = min(kc, k - c0);
+    }
+    int tm, tn;
+    tile_coords<TILE_M, TILE_N>(m, n, tm, tn);
+    const int m0 = tm * TILE_M, n0 = tn * TILE_N;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63, j = lane >> 4, l16 = lane & 15;
+    // the wave's share of k: whole stages, the remainder in the last share
+    const int64_t kw = ((int64_t)k + W * BK - 1) / (W * BK) * BK;
+    const int k0 = (int)min((int64_t)k, wave * kw), k1 = (int)min((int64_t)k, k0 + kw);
+    const auto oa = direct_op<A_KC, TM, WIDE>(A, lda, m0, m, k0);
+    const auto ob = direct_op<B_KC, TN, WIDE>(B, ldb, n0, n, k0);
+
+    d4 acc[TM][TN];
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
+    const int S = (k1 - k0) / BK, left = (k1 - k0) % BK;
+    if (S > 0) {
+        if ((A_KC || m0 + TILE_M <= m) && (B_KC || n0 + TILE_N <= n))
+            direct_stages<A_KC, B_KC, TM, TN, false, WIDE>(oa, ob, S, acc);
+        else
+            direct_stages<A_KC, B_KC, TM, TN, true, WIDE>(oa, ob, S, acc);
+    }
+    if (left > 0) {
+        double fa[TM][4], fb[TN][4];
+        direct_tail<A_KC, TM, WIDE>(oa, S, left, fa);
+        direct_tail<B_KC, TN, WIDE>(ob, S, left, fb);
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int a = 0; a < TM; ++a)
+#pragma unroll
+                for (int b = 0; b < TN; ++b)
+                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a][t], fb[b][t], acc[a][b],
+                                                                     0, 0, 0);
+    }
+    // the waves' partial tiles, added in wave order
+#pragma unroll
+    for (int a = 0; a < TM; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                red[(wave * E + (a * TN + b) * 4 + i) * 64 + lane] = acc[a][b][i];
+    __syncthreads();
+#pragma unroll
+    for (int e0 = 0; e0 < E; e0 += W) {
+        const int e = e0 + wave;
+        double s = red[e * 64 + lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) s += red[(w * E + e) * 64 + lane];
+        const int a = e / (4 * TN), b = e / 4 % TN, q = j + 4 * (e & 3);
+        const int row = m0 + (A_KC ? 16 * a + q : 32 * (a >> 1) + 2 * q + (a & 1));
+        const int col = n0 + (B_KC ? 16 * b + l16 : 32 * (b >> 1) + 2 * l16 + (b & 1));
+        if (row < m && col < n) {
+            double *dst = C + (int64_t)row * ldc + col;
+            *dst = accumulate ? *dst + s : s;
+        }
+    }
+}
+
+// ------------------------------------------------------------- host side
+
+// The kernels a product can run on.
+enum Kernel { kTile, kDirectWide, kDirectSmall };  // 128 x 128; 32 x 64; 32 x 32
+
+// Microseconds of an m x n x k product: full rounds of resident workgroups
+// (two per CU of the first two, four of the last), then the rest with w
+// workgroups per CU, at a share of the CU's 0.307 TFLOP/s that grows with w,
+// plus the launch with its first loads and last stores.  The shares are fits
+// to measured products (us; tile, 32 x 64, 32 x 32): 512^3 71, 13, 8.3;
+// 1024^3 60, 38, 42; 2048^3 309, 262, 332; 4096^3 1930, 1998, -; 1500 x 2777
+// x 2051 (264 tiles) 487, 304, 343.  The direct kernels read both operands of
+// A B^T in 64-byte pieces of many rows, which costs them more (1500 x 2051 x
+// 2777: 340, not 304; 4096^3: 2770).
+double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus) {
+    struct Shape {
+        int bm, bn, per_cu;
+        double one, full, fixed;
+    };
+    const Shape sh = which == kTile         ? Shape{BM, BN, 2, 0.70, 0.90, 8.0}
+                     : which == kDirectWide ? Shape{32, 64, 2, 0.65, nt ? 0.72 : 0.85, 6.0}
+                                            : Shape{32, 32, 4, 0.50, nt ? 0.58 : 0.68, 4.0};
+    const double tiles = (double)((m + sh.bm - 1) / sh.bm) * ((n + sh.bn - 1) / sh.bn);
+    const double one_us = 2.0 * sh.bm * sh.bn * (double)k / 0.307e6;
+    const double rounds = floor(tiles / (sh.per_cu * cus));
+    const double w = ceil((tiles - rounds * sh.per_cu * cus) / cus);
+    double us = sh.fixed + rounds * sh.per_cu * one_us / sh.full;
+    if (w > 0) us += w * one_us / (sh.one + (sh.full - sh.one) * (w - 1) / (sh.per_cu - 1));
+    return us;
+}
+
+int device_cus() {
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return cus;
+}
+
+// Whether every lane's byte offset inside a stage of `outer` rows or columns
+// stays below 2^32.
+bool offsets_fit(bool kc, int outer, int64_t ld) {
+    return (kc ? outer * ld + BK : (int64_t)BK * ld + outer) * 8 < ((int64_t)1 << 32);
+}
+
+Kernel pick_kernel(bool a_kc, bool b_kc, int m, int n, int k, int64_t lda, int64_t ldb) {
+    const int cus = std::max(1, device_cus());
+    const bool nt = a_kc && b_kc;
+    const double wide = kernel_us(kDirectWide, nt, m, n, k, cus);
+    const double small = kernel_us(kDirectSmall, nt, m, n, k, cus);
+    const bool tile_ok = m >= BM && n >= BN && k >= BK && offsets_fit(a_kc, BM, lda) &&
+                         offsets_fit(b_kc, BN, ldb);
+    if (tile_ok && kernel_us(kTile, nt, m, n, k, cus) <= std::min(wide, small)) return kTile;
+    return wide < small ? kDirectWide : kDirectSmall;
+}
+
+template <bool A_KC, bool B_KC, int TM, int TN>
+void launch_direct(int m, int n, int k, const double *A, int64_t lda, const double *B,
+                   int64_t ldb, double *C, int64_t ldc, int accumulate, int kc, int parts,
+                   hipStream_t s) {
+    const int64_t cstride = (int64_t)m * n;
+    const dim3 grid((unsigned)(((m + 16 * TM - 1) / (16 * TM)) * ((n + 16 * TN - 1) / (16 * TN))),
+                    (unsigned)parts);
+    if (offsets_fit(A_KC, std::min(m, 16 * TM), lda) && offsets_fit(B_KC, std::min(n, 16 * TN), ldb))
+        gemm_direct_kernel<A_KC, B_KC, TM, TN, false><<<grid, THREADS, 0, s>>>(
+            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride);
+    else
+        gemm_direct_kernel<A_KC, B_KC, TM, TN, true><<<grid, THREADS, 0, s>>>(
+            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride);
+}
+
 template <bool A_KC, bool B_KC>
 hipError_t launch(int m, int n, int k, const double *A, int64_t lda, const double *B,
                   int64_t ldb, double *C, int64_t ldc, int accumulate, hipStream_t s) {
-    const int tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
-    const int vec_a = (lda % 2 == 0) && (((uintptr_t)A & 15) == 0);
-    const int vec_b = (ldb % 2 == 0) && (((uintptr_t)B & 15) == 0);
-    // the whole-tile path: 16-byte loads, at least one whole stage of k,
-    // every lane's byte offset inside a stage's panel below 2^32, and m, n
-    // at least one tile, so that edge tiles can be moved back to end at m
-    // and n (a move along an operand's contiguous index must keep 16-byte
-    // alignment: m, n even there)
-    const int64_t span_a = (A_KC ? (int64_t)BM * lda : (int64_t)BK * lda) * 8;
-    const int64_t span_b = (B_KC ? (int64_t)BN * ldb : (int64_t)BK * ldb) * 8;
-    const bool full = vec_a && vec_b && m >= BM && n >= BN && k >= BK &&
-                      (A_KC || m % 2 == 0) && (B_KC || n % 2 == 0) &&
-                      span_a < ((int64_t)1 << 32) && span_b < ((int64_t)1 << 32);
-    if (full) {
-        // the whole 16-deep stages of k on the whole-tile path; a last
-        // partial stage (k % 16 terms) is added to C by a guarded launch
-        const int kf = k / BK * BK;
-        {
-            TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, kf, 1, 2.0 * m * n * (double)kf, s);
-            gemm_f64_kernel<A_KC, B_KC, true><<<tiles, THREADS, 0, s>>>(
-                m, n, kf, A, lda, B, ldb, C, ldc, vec_a, vec_b, accumulate);
+    TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, 1, 2.0 * m * n * (double)k, s);
+    switch (pick_kernel(A_KC, B_KC, m, n, k, lda, ldb)) {
+        case kTile: {
+            const int tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
+            gemm_f64_kernel<A_KC, B_KC><<<tiles, THREADS, 0, s>>>(m, n, k, A, lda, B, ldb, C, ldc,
+                                                                 accumulate);
+            break;
         }
-        if (kf < k) {
-            const double *At = A_KC ? A + kf : A + (int64_t)kf * lda;
-            const double *Bt = B_KC ? B + kf : B + (int64_t)kf * ldb;
-            TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k - kf, 1, 2.0 * m * n * (double)(k - kf), s);
-            gemm_f64_kernel<A_KC, B_KC, false><<<tiles, THREADS, 0, s>>>(
-                m, n, k - kf, At, lda, Bt, ldb, C, ldc, vec_a, vec_b, 1);
-        }
-    } else {
-        TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, 1, 2.0 * m * n * (double)k, s);
-        gemm_f64_kernel<A_KC, B_KC, false><<<tiles, THREADS, 0, s>>>(m, n, k, A, lda, B, ldb, C,
-                                                                     ldc, vec_a, vec_b, accumulate);
+        case kDirectWide:
+            launch_direct<A_KC, B_KC, 2, 4>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1, s);
+            break;
+        case kDirectSmall:
+            launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1, s);
+            break;
     }
     return hipGetLastError();
 }
@@ -399,14 +598,28 @@ sum_partials_kernel(int m, int n, int parts, const double *__restrict__ part,
     C[(i / n) * ldc + i % n] = s;
 }
 
-// Chunks of the split contraction: enough workgroups for two rounds of the
-// chip when the output alone has few tiles, each chunk at least 256 deep.
-// 0: no split.
-int split_parts(int m, int n, int k) {
+// Partial products the workspace of tcu_gemm_f64_workspace_bytes has room for
+// (its size is the ABI's): outputs of fewer than 128 tiles of 128 x 128, k at
+// least 1024.  0: none.
+int split_room(int m, int n, int k) {
     const int64_t tiles = (int64_t)((m + BM - 1) / BM) * ((n + BN - 1) / BN);
     if (tiles >= 128 || k < 1024) return 0;
     int64_t parts = (512 + tiles - 1) / tiles;
     parts = std::min<int64_t>(parts, k / 256);
+    return parts >= 2 ? (int)parts : 0;
+}
+
+// Chunks of the split contraction, for outputs of so few 32 x 32 tiles that
+// they leave most CUs idle: one workgroup per CU, each chunk at least 256 deep
+// (four stages per wave; below that the sum's launch costs more than it
+// saves).  64 x 64 x 4096: 38 us in one piece, 9.9 us in 16.  Larger outputs
+// are not split: 1024^3 takes 54 us and 8 for the sum in four chunks of 128 x
+// 128 tiles, 38 us in one piece of 32 x 64 ones.  0: no split.
+int split_parts(int m, int n, int k) {
+    const int64_t tiles = (int64_t)((m + 31) / 32) * ((n + 31) / 32);
+    const int room = split_room(m, n, k);
+    if (tiles > 128 || room == 0) return 0;
+    const int64_t parts = std::min<int64_t>((256 + tiles - 1) / tiles, room);
     return parts >= 2 ? (int)parts : 0;
 }
 
@@ -418,13 +631,9 @@ hipError_t launch_split(int m, int n, int k, const double *A, int64_t lda, const
                         hipStream_t s) {
     const int kc = split_chunk(k, parts);
     const int used = (k + kc - 1) / kc;  // chunks that hold part of k
-    const int tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
-    const int vec_a = (lda % 2 == 0) && (((uintptr_t)A & 15) == 0);
-    const int vec_b = (ldb % 2 == 0) && (((uintptr_t)B & 15) == 0);
     {
         TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, used, 2.0 * m * n * (double)k, s);
-        gemm_f64_kernel<A_KC, B_KC, false><<<dim3(tiles, used), THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, part, n, vec_a, vec_b, 0, kc, (int64_t)m * n);
+        launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, part, n, 0, kc, used, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -437,7 +646,7 @@ hipError_t launch_split(int m, int n, int k, const double *A, int64_t lda, const
 }  // namespace
 
 size_t gemm_f64_split_bytes(int m, int n, int k) {
-    const int parts = split_parts(m, n, k);
+    const int parts = split_room(m, n, k);
     return parts == 0 ? 0 : (size_t)parts * (size_t)m * (size_t)n * sizeof(double);
 }
 
@@ -457,11 +666,8 @@ hipError_t launch_gemm_f64_split(int trans_a, int trans_b, int m, int n, int k, 
 }
 
 int gemm_f64_row_cut(int m, int n) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
-        cus <= 0)
-        return 0;
+    const int cus = device_cus();
+    if (cus <= 0) return 0;
     // two workgroups per CU: each is 4 waves, and the kernel runs 2 waves per SIMD
     const int64_t resident = 2 * (int64_t)cus;
     const int64_t rt = (m + BM - 1) / BM, ct = (n + BN - 1) / BN;
