@@ -102,6 +102,9 @@ typedef struct {
 /* Flags for tcu_workspace_bytes. */
 #define TCU_WS_BACKWARD 1 /* size for tcu_join_agg_bwd as well               */
 #define TCU_WS_COUNT 2    /* size for the optional pair-count output         */
+#define TCU_WS_SCRATCH 4  /* with room for faster encodings of relations
+                             that may repeat cells (optional: a workspace
+                             without it works as well)                       */
 
 /* Flags for tcu_join_agg_bwd. */
 #define TCU_BWD_SAVED_ENCODINGS 1 /* ws still holds X and Y written by the last

@@ -39,6 +39,7 @@ NEED_UNCERTIFIED = 255
 
 TCU_WS_BACKWARD = 1
 TCU_WS_COUNT = 2
+TCU_WS_SCRATCH = 4
 
 TCU_REL_UNIQUE_CELLS = 1
 TCU_NOALLOC_MAX_BYTES = (64 << 20) + (64 << 10)

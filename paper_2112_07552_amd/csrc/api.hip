@@ -258,6 +258,15 @@ EncScratch enc_scratch(void *ws, size_t ws_bytes, const Layout &L, const tcu_rel
     return e;
 }
 
+// Scratch for the encodings of relations that may repeat cells through tiles
+// in LDS (binned.hip), also past the layout's end (TCU_WS_SCRATCH); without
+// it they are placed record by record.
+size_t bin_scratch_bytes(const tcu_relation *A, const tcu_relation *B, int32_t M, int32_t K,
+                         int32_t N, tcu_precision p, bool with_count) {
+    if (A == nullptr || B == nullptr || p != TCU_PREC_FP64) return 0;
+    return binned_scratch_bytes(*A, *B, M, K, N, with_count);
+}
+
 // One relation's encoding on stream s (the matrix zeroed, then the records
 // placed; window by window for large matrices when there is scratch).
 hipError_t encode_one(const tcu_relation &R, int which, int rows, int cols, double *Z,
@@ -666,7 +675,10 @@ size_t tcu_workspace_bytes(const tcu_relation *A, const tcu_relation *B, int32_t
     if (!shapes_ok(M, K, N)) return 0;
     if (!precision_ok(p)) return 0;
     return plan_layout(M, K, N, p, flags, count_planes(A, B, flags)).total +
-           enc_scratch_bytes(A, B, M, K, N);
+           std::max(enc_scratch_bytes(A, B, M, K, N),
+                    (flags & TCU_WS_SCRATCH) != 0
+                        ? bin_scratch_bytes(A, B, M, K, N, p, (flags & TCU_WS_COUNT) != 0)
+                        : 0);
 }
 
 int tcu_mixed_plan(tcu_precision p, int32_t k, double tol, uint32_t need, double u,
@@ -774,10 +786,19 @@ tcu_status tcu::join_agg_fwd_ws(const tcu_relation *A, const tcu_relation *B, in
     double *X = at<double>(ws, L.x), *Y = at<double>(ws, L.y);
     const EncScratch sc = enc_scratch(ws, ws_bytes, L, A, B, M, K, N);
 
+    const size_t bin = bin_scratch_bytes(A, B, M, K, N, p, count != nullptr);
+    const bool binned = bin > 0 && ws_bytes >= L.total + bin;
+    const bool counts = counts_form(A, B, M, K, N, p);
     TCU_TRY(launch_clear_status(st, stream));
-    if (counts_form(A, B, M, K, N, p))
+    if (counts)
         return hip_status(launch_count(*A, *B, M, K, N, at<int8_t>(ws, L.x), at<int8_t>(ws, L.y),
                                        st, C, count, stream));
+    if (binned) {
+        TCU_TRY(launch_binned(*A, *B, M, K, N, X, Y, count, C, st,
+                              static_cast<char *>(ws) + L.total, stream));
+        TCU_TRY(launch_gemm_f64_split(0, 0, M, N, K, X, K, Y, N, C, N, split_part(ws, L), stream));
+        return TCU_OK;
+    }
     if (planes) {
         // exact pair counts, Section 3.1's 0/1 encodings (unique cells): one
         // int8 product with exact int32 sums (K < 2^31)

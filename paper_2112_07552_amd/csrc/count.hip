@@ -163,6 +163,12 @@ hipError_t launch_count(const tcu_relation &A, const tcu_relation &B, int M, int
     if (n > 0)
         count_planes_kernel<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(
             A.n, A.group, A.key, B.n, B.group, B.key, M, N, K, qa, alp, qb, blp, st);
+    return launch_count_planes_product(M, K, N, qa, qb, C, cnt, s);
+}
+
+hipError_t launch_count_planes_product(int M, int K, int N, const int8_t *qa, const int8_t *qb,
+                                       double *C, int32_t *cnt, hipStream_t s) {
+    const int alp = (int)count_lines_pad(M), blp = (int)count_lines_pad(N);
     TraceScope ts(TCU_KERNEL_COUNT, M, N, K, 1, 2.0 * M * N * (double)K, s);
     const int tiles_n = blp / BN, nblk = (K + 31) / 32;
     const unsigned grid = (unsigned)((int64_t)(alp / BM) * tiles_n);

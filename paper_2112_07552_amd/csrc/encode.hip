@@ -325,7 +325,8 @@ window_scatter_kernel(const unsigned long long *__restrict__ offsets, int w,
 
 __global__ void __launch_bounds__(kThreads)
 f64_to_i32_kernel(const double *__restrict__ src, int32_t *__restrict__ dst, size_t n,
-                  StatusBlock *st) {
+                  StatusBlock *st, const uint32_t *only_if) {
+    if (only_if != nullptr && *only_if == 0u) return;
     const size_t stride = (size_t)gridDim.x * kThreads;
     bool over = false;
     for (size_t i = (size_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += stride) {
@@ -537,9 +538,9 @@ hipError_t launch_gather(const tcu_relation &R, int transpose, int rows, int col
 }
 
 hipError_t launch_f64_to_i32(const double *src, int32_t *dst, size_t n, StatusBlock *st,
-                             hipStream_t s) {
+                             hipStream_t s, const uint32_t *only_if) {
     if (n == 0) return hipSuccess;
-    f64_to_i32_kernel<<<capped_grid(n), kThreads, 0, s>>>(src, dst, n, st);
+    f64_to_i32_kernel<<<capped_grid(n), kThreads, 0, s>>>(src, dst, n, st, only_if);
     return hipGetLastError();
 }
 

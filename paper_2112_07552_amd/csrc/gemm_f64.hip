@@ -211,7 +211,8 @@ template <bool A_KC, bool B_KC>
 __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
                 const double *__restrict__ B, int64_t ldb, double *__restrict__ C, int64_t ldc,
-                int accumulate) {
+                int accumulate, const uint32_t *only_if) {
+    if (only_if != nullptr && *only_if == 0u) return;
     __shared__ __attribute__((aligned(16))) double lds_a[2][Tile<A_KC>::elems];
     __shared__ __attribute__((aligned(16))) double lds_b[2][Tile<B_KC>::elems];
 
@@ -421,7 +422,9 @@ template <bool A_KC, bool B_KC, int TM, int TN, bool WIDE>
 __global__ void __launch_bounds__(THREADS)
 gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
                    const double *__restrict__ B, int64_t ldb, double *__restrict__ C,
-                   int64_t ldc, int accumulate, int kc, int64_t cstride) {
+                   int64_t ldc, int accumulate, int kc, int64_t cstride,
+                   const uint32_t *only_if) {
+    if (only_if != nullptr && *only_if == 0u) return;
     constexpr int TILE_M = 16 * TM, TILE_N = 16 * TN, W = THREADS / 64, E = 4 * TM * TN;
     static_assert((A_KC || TM % 2 == 0) && (B_KC || TN % 2 == 0), "pairs of blocks");
     __shared__ double red[W * E * 64];
@@ -552,34 +555,37 @@ Kernel pick_kernel(bool a_kc, bool b_kc, int m, int n, int k, int64_t lda, int64
 template <bool A_KC, bool B_KC, int TM, int TN>
 void launch_direct(int m, int n, int k, const double *A, int64_t lda, const double *B,
                    int64_t ldb, double *C, int64_t ldc, int accumulate, int kc, int parts,
-                   hipStream_t s) {
+                   const uint32_t *only_if, hipStream_t s) {
     const int64_t cstride = (int64_t)m * n;
     const dim3 grid((unsigned)(((m + 16 * TM - 1) / (16 * TM)) * ((n + 16 * TN - 1) / (16 * TN))),
                     (unsigned)parts);
     if (offsets_fit(A_KC, std::min(m, 16 * TM), lda) && offsets_fit(B_KC, std::min(n, 16 * TN), ldb))
         gemm_direct_kernel<A_KC, B_KC, TM, TN, false><<<grid, THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride);
+            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, only_if);
     else
         gemm_direct_kernel<A_KC, B_KC, TM, TN, true><<<grid, THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride);
+            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, only_if);
 }
 
 template <bool A_KC, bool B_KC>
 hipError_t launch(int m, int n, int k, const double *A, int64_t lda, const double *B,
-                  int64_t ldb, double *C, int64_t ldc, int accumulate, hipStream_t s) {
+                  int64_t ldb, double *C, int64_t ldc, int accumulate, const uint32_t *only_if,
+                  hipStream_t s) {
     TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, 1, 2.0 * m * n * (double)k, s);
     switch (pick_kernel(A_KC, B_KC, m, n, k, lda, ldb)) {
         case kTile: {
             const int tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
             gemm_f64_kernel<A_KC, B_KC><<<tiles, THREADS, 0, s>>>(m, n, k, A, lda, B, ldb, C, ldc,
-                                                                 accumulate);
+                                                                 accumulate, only_if);
             break;
         }
         case kDirectWide:
-            launch_direct<A_KC, B_KC, 2, 4>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1, s);
+            launch_direct<A_KC, B_KC, 2, 4>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1,
+                                            only_if, s);
             break;
         case kDirectSmall:
-            launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1, s);
+            launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1,
+                                            only_if, s);
             break;
     }
     return hipGetLastError();
@@ -633,7 +639,7 @@ hipError_t launch_split(int m, int n, int k, const double *A, int64_t lda, const
     const int used = (k + kc - 1) / kc;  // chunks that hold part of k
     {
         TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, used, 2.0 * m * n * (double)k, s);
-        launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, part, n, 0, kc, used, s);
+        launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, part, n, 0, kc, used, nullptr, s);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -686,15 +692,15 @@ int gemm_f64_row_cut(int m, int n) {
 
 hipError_t launch_gemm_f64(int trans_a, int trans_b, int m, int n, int k, const double *A,
                            int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
-                           hipStream_t s, int accumulate) {
+                           hipStream_t s, int accumulate, const uint32_t *only_if) {
     if (m == 0 || n == 0) return hipSuccess;
     if (!trans_a && !trans_b)
-        return launch<true, false>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, s);
+        return launch<true, false>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, only_if, s);
     if (!trans_a && trans_b)
-        return launch<true, true>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, s);
+        return launch<true, true>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, only_if, s);
     if (trans_a && !trans_b)
-        return launch<false, false>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, s);
-    return launch<false, true>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, s);
+        return launch<false, false>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, only_if, s);
+    return launch<false, true>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, only_if, s);
 }
 
 }  // namespace tcu

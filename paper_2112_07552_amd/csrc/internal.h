@@ -27,7 +27,8 @@ struct StatusBlock {
     uint32_t exc_seg[4];            // exception scan: cells listed per segment (kExcThresholds;
                                     // above the segment's capacity: it overflowed)
     uint32_t exceptions;            // residue form: cells of the last product recomputed alone
-    uint32_t pad[43];
+    uint32_t wide_counts;           // a cell's multiplicity exceeds int8 (binned encodings)
+    uint32_t pad[42];
 };
 static_assert(sizeof(StatusBlock) == 256, "status block must be 256 bytes");
 constexpr int kExcThresholds = 4;  // thresholds the exception scan counts above
@@ -115,8 +116,10 @@ hipError_t launch_gather(const tcu_relation &R, int transpose, int rows, int col
                          int r1 = -1);
 // counts held in FP64 to int32; values above INT32_MAX are stored as
 // INT32_MAX and set kFlagCountRange
+// (only_if, here and below: a device word; the kernels leave at once when it
+// is 0.  NULL: they run)
 hipError_t launch_f64_to_i32(const double *src, int32_t *dst, size_t n, StatusBlock *st,
-                             hipStream_t s);
+                             hipStream_t s, const uint32_t *only_if = nullptr);
 
 // split.hip: per-line max |z| (axis 0: rows, 1: columns) into maxbits (bit
 // patterns of non-negative doubles), the sums of |z| (sums may be NULL), and
@@ -151,7 +154,7 @@ int split_chunk_steps(int S, int digit_bf16);
 // accumulate != 0, C += op(A) * op(B).
 hipError_t launch_gemm_f64(int trans_a, int trans_b, int m, int n, int k, const double *A,
                            int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
-                           hipStream_t s, int accumulate = 0);
+                           hipStream_t s, int accumulate = 0, const uint32_t *only_if = nullptr);
 // The same product with the contraction split into chunks whose partial
 // products go to `part` and are summed in chunk order, when the output has
 // too few tiles to fill the chip (gemm_f64_split_bytes > 0); otherwise (or
@@ -173,9 +176,24 @@ int gemm_f64_row_cut(int m, int n);
 // Records outside the shape are counted in st (NULL: not counted).  M and N
 // at most 2^30.
 size_t count_plane_bytes(int64_t lines, int64_t len);
+int64_t count_lines_pad(int64_t lines);
+// The product alone, of planes of any int8 values (K times the square of the
+// largest below 2^31).
+hipError_t launch_count_planes_product(int M, int K, int N, const int8_t *qa, const int8_t *qb,
+                                       double *C, int32_t *cnt, hipStream_t s);
 hipError_t launch_count(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
                         int8_t *qa, int8_t *qb, StatusBlock *st, double *C, int32_t *cnt,
                         hipStream_t s);
+
+// binned.hip: X and Y of two relations that both may repeat cells, and with
+// count != NULL the exact pair counts (M x N; C, M x N, is scratch then, and X
+// and Y hold the sums afterwards), through tiles summed in LDS.  scratch:
+// binned_scratch_bytes (0: this form does not take the call), 256-byte aligned.
+size_t binned_scratch_bytes(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                            bool planes);
+hipError_t launch_binned(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                         double *X, double *Y, int32_t *count, double *C, StatusBlock *st,
+                         void *scratch, hipStream_t s);
 
 // dict.hip: dictionary encoding (ranks in the sorted union of two columns).
 size_t dict_workspace_bytes(int64_t n);

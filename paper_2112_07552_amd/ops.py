@@ -74,8 +74,9 @@ def make_relation(group: torch.Tensor, key: torch.Tensor, val: Optional[torch.Te
 
 
 def workspace_bytes(A, B, M: int, K: int, N: int, precision: str = "fp64",
-                    backward: bool = False, count: bool = False) -> int:
-    flags = (_lib.TCU_WS_BACKWARD if backward else 0) | (_lib.TCU_WS_COUNT if count else 0)
+                    backward: bool = False, count: bool = False, scratch: bool = False) -> int:
+    flags = ((_lib.TCU_WS_BACKWARD if backward else 0) | (_lib.TCU_WS_COUNT if count else 0) |
+             (_lib.TCU_WS_SCRATCH if scratch else 0))
     nb = _lib.load().tcu_workspace_bytes(C.byref(A), C.byref(B), M, K, N,
                                           PRECISIONS[precision], flags)
     if nb == 0:
@@ -221,9 +222,9 @@ def join_agg_fwd(a_group, a_key, a_val, b_key, b_group, b_val, M: int, K: int, N
     A = make_relation(a_group, a_key, a_val, unique)
     B = make_relation(b_group, b_key, b_val, unique)
     dev = a_group.device
-    need = workspace_bytes(A, B, M, K, N, precision, count=with_count, backward=for_backward)
-    if ws is None or ws.numel() < need:
-        ws = alloc_workspace(need, dev)
+    flags = dict(count=with_count, backward=for_backward)
+    if ws is None or ws.numel() < workspace_bytes(A, B, M, K, N, precision, **flags):
+        ws = alloc_workspace(workspace_bytes(A, B, M, K, N, precision, scratch=True, **flags), dev)
     Cm = torch.empty((M, N), dtype=torch.float64, device=dev)
     cnt = torch.empty((M, N), dtype=torch.int32, device=dev) if with_count else None
     check(_lib.load().tcu_join_agg_fwd(C.byref(A), C.byref(B), M, K, N, PRECISIONS[precision],
