@@ -789,6 +789,11 @@ tcu_status tcu::join_agg_fwd_ws(const tcu_relation *A, const tcu_relation *B, in
     const size_t bin = bin_scratch_bytes(A, B, M, K, N, p, count != nullptr);
     const bool binned = bin > 0 && ws_bytes >= L.total + bin;
     const bool counts = counts_form(A, B, M, K, N, p);
+    if (!is_split(p) && count == nullptr && !counts && !binned && encode_pair_fits(M, K, N)) {
+        TCU_TRY(launch_encode_pair(*A, *B, M, K, N, X, Y, st, stream));
+        TCU_TRY(launch_gemm_f64_split(0, 0, M, N, K, X, K, Y, N, C, N, split_part(ws, L), stream));
+        return TCU_OK;
+    }
     TCU_TRY(launch_clear_status(st, stream));
     if (counts)
         return hip_status(launch_count(*A, *B, M, K, N, at<int8_t>(ws, L.x), at<int8_t>(ws, L.y),

@@ -108,6 +108,13 @@ size_t encode_scratch_bytes(const tcu_relation &R, int rows, int cols);
 hipError_t launch_encode_zeroed(const tcu_relation &R, int transpose, int rows, int cols,
                                 double *out, StatusBlock *st, int which, void *scratch,
                                 size_t scratch_bytes, hipStream_t s);
+// Both encodings of a join whose workspace holds the status block, X and Y one
+// after the other: all of it zeroed (the status block cleared with it) in one
+// launch, both relations placed in another.  For small matrices
+// (encode_pair_fits), where launches are the time.
+bool encode_pair_fits(int M, int K, int N);
+hipError_t launch_encode_pair(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                              double *X, double *Y, StatusBlock *st, hipStream_t s);
 // dst[i] = src[row_i, col_i] for the records whose row lies in [r0, r1)
 // (r1 < 0: all rows); the launch with r0 = 0 also writes 0 for records
 // outside the matrix.
