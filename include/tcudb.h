@@ -206,7 +206,11 @@ size_t tcu_encode_workspace_bytes(const tcu_relation *R, int32_t rows, int32_t c
  * 211, 199, 197); TCU_ERR_INFEASIBLE when no plan exists (then the product
  * runs in FP64 and TCU_FLAG_FALLBACK is set), tol < 2^-50, or the residue
  * form with k > 131071 (int32 sums); TCU_ERR_ARG for a bad precision or
- * k < 1.  tol <= 0 means 1e-12.  Host only: touches no device. */
+ * k < 1.  tol <= 0 means 1e-12.  Host only: touches no device.
+ * A residue-form product of 2^30 multiply-adds or more takes its width from
+ * this plan and its moduli from the smaller of u and the largest over the
+ * cells of 2^-14 (T + 128 (s_g + s_h)), which bounds |sum_k x'y'| 2^-2b too:
+ * fewer moduli, the same integers. */
 int tcu_mixed_plan(tcu_precision p, int32_t k, double tol, uint32_t need, double u,
                    int32_t *bits);
 

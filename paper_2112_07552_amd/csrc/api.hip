@@ -358,6 +358,11 @@ int crt_moduli_for(int32_t k, double tol, int b, double u) {
     return r > 0 ? r : 0;
 }
 
+// Multiply-adds from which the moduli follow the cells' bound as well as the
+// line sums': below, one modulus (0.9 us of matrix-core time at 2^30) is lost
+// in the launches, and the plan is tcu_mixed_plan's of the line sums.
+constexpr double kCellBoundWork = 0x1p30;
+
 // Estimated seconds of the residue products (L moduli) of an m x n x k
 // product and of the FP64 product that replaces a plan without moduli
 // (L = 0); of the scan, which reads the need plane and synchronises once
@@ -467,6 +472,7 @@ hipError_t certify_and_plan(int m, int n, int k, tcu_precision p, double tol, vo
         ca.need_plane = at<uint8_t>(ws, L.need);
         ca.need_cert = &st->need_cert;
         ca.need_min = &st->need_min;
+        ca.ucell = &st->ucell;
     }
     hipError_t e = launch_certify(m, n, k, at<int8_t>(ws, L.qa), (int)pad256(m),
                                   at<int8_t>(ws, L.qb), (int)padB(n), (int)qlen(k), ca,
@@ -509,6 +515,14 @@ hipError_t certify_and_plan(int m, int n, int k, tcu_precision p, double tol, vo
                 mp->exc_last = xp.last;
             }
         }
+    }
+    if (is_crt(p) && r > 0 && (double)m * n * k >= kCellBoundWork) {
+        // the width stays; the moduli need hold no more than the cells' bound
+        float uc;
+        memcpy(&uc, &host.ucell, sizeof(uc));
+        const double u = std::min(std::min(ua, ub), (double)uc * 0x1p-14 * (1.0 + 0x1p-20));
+        const int rc = crt_moduli_for(k, tol, bits, u);
+        if (rc > 0) r = std::min(r, rc);
     }
     if (r > 0) {
         mp->S = r;

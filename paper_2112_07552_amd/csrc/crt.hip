@@ -337,6 +337,15 @@ mag_cols_kernel(const double *__restrict__ Z, int rows, int cols, int64_t ld,
 // where tcrt and tdig[S] are the tolerance less the rounding of the FP64
 // combination.  The cell's need is the smallest such b and S; a cell with T
 // = 0 but r > 0 cannot be bounded (kNeedUncertified).
+// The same sums bound the integer product from above: with |z| 2^(7 - e) = q +
+// f, 0 <= f < 1, each term (q_x + f_x)(q_y + f_y) is at most q_x q_y + 128
+// (|x| 2^-e + |y| 2^-f'), so 2^14 times the normalised (|X||Y|)[g,h] is at most
+// T + 128 (s_g + s_h), and at most 2^14 min(s_g, s_h), as every normalised
+// value is below 1.  The largest of these over the cells (rounded to float;
+// the plan adds 2^-20) is what the modulus product has to hold: 2^3.4 against
+// 2^7.3 by the line sums alone at 4096^3 log-uniform values, where 13 moduli
+// then do for 14; 2^2.8 against 2^7.6 at 16384^3 of the outlier mixture, 14 for
+// 15.
 // The residue form's need of one cell: the smallest b >= 1 with r <= 2^b u,
 // u = tcrt T, read off the exponents and mantissas of r (enlarged past the
 // rounding of u) and u: with r = mr 2^er and u = mu 2^eu (mantissas in
@@ -691,6 +700,7 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
         // the largest and the smallest nonzero need among the cells the
         // certificate bounds.
         uint32_t need = 0, cneed = 0, mneed = kNeedUncertified;
+        float ucell = 0.0f;
 #pragma unroll
         for (int a = 0; a < WA; ++a) {
             const int rbase = m0 + wm * 32 * WA + a * 32;
@@ -711,6 +721,9 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
                     const double r = (sx > 0.0 && sy > 0.0) ? 16384.0 * (sx + sy) : 0.0;
                     const uint32_t c = EPI == kEpiCertify ? cert_bits(r, acc[a][b][i], ca)
                                                           : cert_slices(r, acc[a][b][i], ca);
+                    if (EPI == kEpiCertify && r > 0.0)
+                        ucell = fmaxf(ucell, fminf(fmaf((float)r, 0x1p-7f, (float)acc[a][b][i]),
+                                                   16384.0f * (float)fmin(sx, sy)));
                     need = max(need, c);
                     if (c < kNeedUncertified) cneed = max(cneed, c);
                     if (c > 0) mneed = min(mneed, c);
@@ -726,6 +739,7 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
             need = max(need, (uint32_t)__shfl_xor((int)need, off));
             cneed = max(cneed, (uint32_t)__shfl_xor((int)cneed, off));
             mneed = min(mneed, (uint32_t)__shfl_xor((int)mneed, off));
+            ucell = fmaxf(ucell, __shfl_xor(ucell, off));
         }
         // Every workgroup of the launch ends here at about the same time, and
         // same-address atomics from all of them serialise.  The waves' values
@@ -739,6 +753,7 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
             red[wave] = need;
             red[G::NW + wave] = cneed;
             red[2 * G::NW + wave] = mneed;
+            red[3 * G::NW + wave] = __float_as_uint(ucell);
         }
         __syncthreads();
         if (threadIdx.x == 0) {
@@ -746,6 +761,7 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
                 need = max(need, red[w]);
                 cneed = max(cneed, red[G::NW + w]);
                 mneed = min(mneed, red[2 * G::NW + w]);
+                ucell = fmaxf(ucell, __uint_as_float(red[3 * G::NW + w]));
             }
             uint32_t *nb = EPI == kEpiCertify ? ca.need_bits : ca.need_slices;
             if (need > __atomic_load_n(nb, __ATOMIC_RELAXED)) atomicMax(nb, need);
@@ -755,6 +771,10 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
             if (EPI == kEpiCertify && ca.need_min != nullptr && mneed < kNeedUncertified &&
                 mneed < __atomic_load_n(ca.need_min, __ATOMIC_RELAXED))
                 atomicMin(ca.need_min, mneed);
+            // (bit patterns of non-negative floats order as they do)
+            if (EPI == kEpiCertify && ca.ucell != nullptr &&
+                __float_as_uint(ucell) > __atomic_load_n(ca.ucell, __ATOMIC_RELAXED))
+                atomicMax(ca.ucell, __float_as_uint(ucell));
         }
         return;
     }

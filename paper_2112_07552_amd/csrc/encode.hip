@@ -46,6 +46,7 @@ __global__ void reset_plan_kernel(StatusBlock *st) {
     st->umax_b = 0;
     st->need_cert = 0;
     st->need_min = kNeedUncertified;
+    st->ucell = 0;
     for (int j = 0; j < kExcThresholds; ++j) st->exc_seg[j] = 0;
     st->exceptions = 0;
 }

@@ -28,7 +28,9 @@ struct StatusBlock {
                                     // above the segment's capacity: it overflowed)
     uint32_t exceptions;            // residue form: cells of the last product recomputed alone
     uint32_t wide_counts;           // a cell's multiplicity exceeds int8 (binned encodings)
-    uint32_t pad[42];
+    uint32_t ucell;                 // certificate: bits of the largest float 2^14 bound of a
+                                    // cell's normalised sum of |x||y|
+    uint32_t pad[41];
 };
 static_assert(sizeof(StatusBlock) == 256, "status block must be 256 bytes");
 constexpr int kExcThresholds = 4;  // thresholds the exception scan counts above
@@ -261,6 +263,9 @@ struct CertArgs {
     // nonzero need among the cells the certificate bounds; may be NULL
     uint8_t *need_plane;
     uint32_t *need_cert, *need_min;
+    // residue form: the largest over all cells of a bound, in units of
+    // 2^(e_g + f_h - 14), on (|X||Y|)[g,h] (float bits); may be NULL
+    uint32_t *ucell;
 };
 hipError_t launch_mag_plane(const double *Z, int rows, int cols, int64_t ld, int axis,
                             const unsigned long long *maxbits, const double *sums, double *shat,
