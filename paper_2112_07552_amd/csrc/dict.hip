@@ -10,21 +10,22 @@
 // Steps (all on the caller's stream):
 //  1. insert every value into an open-addressing hash set (linear probing,
 //     64-bit compare-and-swap);
-//  2. compact the occupied slots into a list of the distinct values;
-//  3. sort that list: chunks of 2048 in LDS, then merges of eight runs at a
-//     time, each value finding its place by binary search in the other runs;
-//  4. write each distinct value's rank into a code array parallel to the
-//     table, then look every record's value up.
-// Every kernel reads the number of distinct values from device memory, so
-// the whole sequence is enqueued at once and the host waits only at the end,
-// for the count it returns.  The first attempt uses a table of at most 2^18
-// slots (3 MB with its codes, which an XCD's L2 holds), whatever the column
-// length: clearing and scanning a table sized for 2^25 values with 32
-// distinct ones took 270 us, with this one 8 us.  When the values do not fit
-// (a probe sequence of kSmallProbes slots, or more than half of the slots
-// taken) the remaining kernels of the attempt leave at once and the sequence
-// runs again, with 2^21 slots and then with twice as many slots as values,
-// where every probe sequence meets a free slot.
+//  2. up to kSmallDict distinct values: one workgroup sorts them in LDS and
+//     writes each one's rank into a code array parallel to the table; every
+//     record's value is then looked up;
+//  3. the host waits, for the count it returns;
+//  4. with more distinct values only then, and with grids of that count: the
+//     occupied slots compacted into a list, the list sorted (chunks of 2048 in
+//     LDS, then merges of eight runs at a time, each value finding its place
+//     by binary search in the other runs), ranks and codes as above.
+// So a dictionary of few values takes four launches, any other up to ten, and
+// neither waits twice.  The first attempt uses a table of at most 2^18 slots
+// (3 MB with its codes, which an XCD's L2 holds), whatever the column length:
+// clearing and scanning a table sized for 2^25 values with 32 distinct ones
+// took 270 us, clearing this one 4 us.  When the values do not fit (a probe
+// sequence of kSmallProbes slots, or more than half of the slots taken) the
+// insertion is run again, with 2^21 slots and then with twice as many slots as
+// values, where every probe sequence meets a free slot.
 //
 // INT64_MIN marks an empty slot; a column value equal to INT64_MIN is
 // handled apart (it is the smallest value, so it gets code 0 when present).
@@ -60,6 +61,7 @@ struct DictState {
     unsigned long long count;  // distinct values other than INT64_MIN
     unsigned int has_min;      // INT64_MIN occurs
     unsigned int overflow;     // a probe sequence ran out: the table is too small
+    unsigned int listed;       // places taken in the compacted list
 };
 
 // One attempt: the table, the most distinct values it may hold, and the
@@ -70,8 +72,13 @@ struct Table {
     unsigned long long mask, max_probes, max_count;
 };
 
-// What every kernel after the insertion does first: the number of distinct
-// values, or 0 when this attempt failed.
+// Up to this many distinct values one workgroup sorts them (the insertion
+// lists their slots in LDS; a list of twice as many would cost it one of its
+// four workgroups per CU).
+constexpr int kSmallDict = 1024;
+
+// What the sort's kernels do first: the number of distinct values, or 0 when
+// this attempt failed.
 __device__ inline int64_t live_count(const DictState *st, const Table &t) {
     const unsigned long long c = st->count;
     return (st->overflow || c > t.max_count) ? 0 : (int64_t)c;
@@ -85,6 +92,20 @@ __global__ void dict_clear_kernel(Table t, DictState *st) {
         st->count = 0;
         st->has_min = 0;
         st->overflow = 0;
+        st->listed = 0;
+    }
+}
+
+// After step (kk, j) of a bitonic sort with one pair per thread: a wave's 64
+// pairs at distance j <= 64 are 128 neighbouring values, its own, so the
+// workgroup meets only around wider steps (2048 values: 20 us with a barrier
+// after every step).
+__device__ inline void step_barrier(int kk, int j) {
+    if (max(j, j > 1 ? j / 2 : kk) > 64) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
 }
 
@@ -93,23 +114,27 @@ __global__ void dict_clear_kernel(Table t, DictState *st) {
 // touches the table a few times per workgroup instead of once per record:
 // 2^24 values with 32 distinct took 300 us against 46 us here (2.9 TB/s of
 // the column).  Columns with many distinct values mostly miss and go to the
-// table: 2^25 values with 5000 distinct 584 us for the whole encoding, with
-// 32 distinct 222 us (before 1008 and 884 us).
-constexpr int kInsThreads = 512;
+// table.
+constexpr int kInsThreads = 512, kSmallThreads = 512;
 constexpr int kSeenBits = 12;       // LDS entries: 4096 (32 KB)
 constexpr unsigned kSeen = 1u << kSeenBits;
 
 // PER: values per thread and round, loaded together.  Columns too short to
 // fill the chip that way take one per thread: a value's probes are a chain of
 // memory round trips.
+// `mine` lists the slots this workgroup has filled, while they are few; each
+// workgroup adds its number to the count and, as long as all of them are at
+// most kSmallDict, its slots to `list`.
 template <int PER>
 __global__ void __launch_bounds__(kInsThreads)
 dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long *__restrict__ b,
-                   int64_t n, Table t, DictState *st) {
+                   int64_t n, Table t, unsigned int *__restrict__ list, DictState *st) {
     __shared__ unsigned long long seen[kSeen];
-    __shared__ unsigned int seen_min, full;
+    __shared__ unsigned int mine[kSmallDict];
+    __shared__ unsigned int seen_min, full, filled;
+    __shared__ unsigned long long base;
     for (unsigned i = threadIdx.x; i < kSeen; i += kInsThreads) seen[i] = kEmpty;
-    if (threadIdx.x == 0) seen_min = full = 0u;
+    if (threadIdx.x == 0) seen_min = full = filled = 0u;
     __syncthreads();
     const int64_t step = (int64_t)gridDim.x * kInsThreads * PER;
     for (int64_t i0 = (int64_t)blockIdx.x * kInsThreads * PER; i0 < n; i0 += step) {
@@ -117,7 +142,7 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
         if (threadIdx.x == 0 &&
             __hip_atomic_load(&st->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
             __hip_atomic_store(&full, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        if (__hip_atomic_load(&full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) return;
+        if (__hip_atomic_load(&full, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) break;
         unsigned long long v[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
@@ -134,14 +159,15 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
                 }
                 continue;
             }
-            unsigned long long *mine = seen + lds_hash(v[j], kSeenBits);
+            unsigned long long *slot_seen = seen + lds_hash(v[j], kSeenBits);
             // An entry holding v was put there by the thread that inserts v:
             // the exchange lets one thread of the workgroup through, so that
             // at the kernel's start not every wave goes to the same few slots
             // (2^25 + 2^24 values, 32 distinct: 139 us; with a plain store
             // after the insertion 527 us)
-            if (__hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) == v[j] ||
-                atomicExch(mine, v[j]) == v[j])
+            if (__hip_atomic_load(slot_seen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) ==
+                    v[j] ||
+                atomicExch(slot_seen, v[j]) == v[j])
                 continue;
             unsigned long long h = fmix64(v[j]) & t.mask;
             unsigned long long probe = 0;
@@ -154,12 +180,69 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
                 if (got == v[j]) break;
                 if (got == kEmpty) {
                     const unsigned long long prev = atomicCAS(t.slot + h, kEmpty, v[j]);
-                    if (prev == kEmpty || prev == v[j]) break;
+                    if (prev == kEmpty) {
+                        const unsigned int q = atomicAdd(&filled, 1u);
+                        if (q < (unsigned)kSmallDict) mine[q] = (unsigned int)h;
+                        break;
+                    }
+                    if (prev == v[j]) break;
                 }
                 h = (h + 1) & t.mask;
             }
             if (probe == t.max_probes) atomicOr(&st->overflow, 1u);
         }
+    }
+    __syncthreads();
+    const unsigned int got = filled;
+    if (threadIdx.x == 0 && got > 0u) base = atomicAdd(&st->count, (unsigned long long)got);
+    __syncthreads();
+    if (got > 0u && base + got <= (unsigned long long)kSmallDict)
+        for (unsigned int i = threadIdx.x; i < got; i += kInsThreads) list[base + i] = mine[i];
+}
+
+// A small dictionary, by one workgroup: the listed slots' values sorted, slots
+// along with them, written to dict, and their ranks to the slots' codes.
+// (Done by the insertion's last workgroup to finish, this saved a launch and
+// cost 40 us at 2^24 values, for a count of finished workgroups and fences.)
+__global__ void __launch_bounds__(kSmallThreads)
+dict_small_kernel(Table t, const unsigned int *__restrict__ list, const DictState *st,
+                  long long *__restrict__ dict) {
+    __shared__ long long val[kSmallDict];
+    __shared__ unsigned int slots[kSmallDict];
+    const unsigned long long k = st->count;
+    if (st->overflow || k > (unsigned long long)kSmallDict) return;
+    int P = 2;
+    while (P < (int)k) P *= 2;
+    for (int i = threadIdx.x; i < P; i += kSmallThreads) {
+        // padding: after every value, also one that equals it
+        const unsigned int slot = i < (int)k ? list[i] : 0xffffffffu;
+        val[i] = i < (int)k ? (long long)t.slot[slot] : 0x7fffffffffffffffll;
+        slots[i] = slot;
+    }
+    __syncthreads();
+    static_assert(kSmallDict <= 2 * kSmallThreads, "one pair per thread");
+    for (int kk = 2; kk <= P; kk *= 2)
+        for (int j = kk / 2; j > 0; j /= 2) {
+            const int p = threadIdx.x;
+            if (p < P / 2) {
+                const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1)), l = i + j;
+                const long long x = val[i], y = val[l];
+                const unsigned int sx = slots[i], sy = slots[l];
+                if ((x > y || (x == y && sx > sy)) == ((i & kk) == 0)) {
+                    val[i] = y;
+                    val[l] = x;
+                    slots[i] = sy;
+                    slots[l] = sx;
+                }
+            }
+            step_barrier(kk, j);
+        }
+    __syncthreads();
+    const int shift = st->has_min ? 1 : 0;
+    if (threadIdx.x == 0 && shift) dict[0] = (long long)kEmpty;
+    for (int i = threadIdx.x; i < (int)k; i += kSmallThreads) {
+        dict[i + shift] = val[i];
+        t.code[slots[i]] = i + shift;
     }
 }
 
@@ -170,8 +253,7 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
 template <int PER>
 __global__ void __launch_bounds__(kThreads)
 dict_compact_kernel(Table t, long long *__restrict__ distinct, DictState *st) {
-    __shared__ unsigned int wave_sum[kThreads / 64];
-    __shared__ unsigned long long base;
+    __shared__ unsigned int wave_sum[kThreads / 64], base;
     if (st->overflow) return;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t i0 = (size_t)blockIdx.x * kThreads * PER + threadIdx.x;
@@ -199,10 +281,10 @@ dict_compact_kernel(Table t, long long *__restrict__ distinct, DictState *st) {
             wave_sum[w] = all;
             all += c;
         }
-        base = all ? atomicAdd(&st->count, (unsigned long long)all) : 0ull;
+        base = all ? atomicAdd(&st->listed, all) : 0u;
     }
     __syncthreads();
-    unsigned long long at = base + wave_sum[wave] + (incl - mine);
+    unsigned int at = base + wave_sum[wave] + (incl - mine);
 #pragma unroll
     for (int j = 0; j < PER; ++j)
         if (v[j] != kEmpty && at < t.max_count) distinct[at++] = (long long)v[j];
@@ -249,15 +331,7 @@ dict_sort_runs_kernel(long long *__restrict__ sorted, long long *__restrict__ ot
                     v[l] = x;
                 }
             }
-            // a wave's 64 pairs at distance j <= 64 are 128 neighbouring
-            // values, its own: the workgroup meets only around wider steps
-            // (2048 values: 20 us with a barrier after every step)
-            if (max(j, j > 1 ? j / 2 : kk) > 64) {
-                __syncthreads();
-            } else {
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-            }
+            step_barrier(kk, j);
         }
     __syncthreads();
     long long *dst = (merge_passes(k) & 1) ? other : sorted;
@@ -329,7 +403,7 @@ dict_rank_kernel(const long long *__restrict__ sorted, Table t, const DictState 
     if (s >= 0) t.code[s] = (int)(r + shift);
 }
 
-// Codes of both columns.  A dictionary of at most kLdsDict values is put into
+// Codes of both columns, if the dictionary has at most `limit` values.  A dictionary of at most kLdsDict values is put into
 // an LDS hash table by each workgroup when the columns are long enough to
 // repay it (kLdsMinN): 2^24 records with 32 distinct values 38 us (5.3 TB/s)
 // against 72 us through the table in memory.
@@ -342,11 +416,12 @@ constexpr int64_t kLdsMinN = (int64_t)1 << 19;
 template <int PER>
 __global__ void __launch_bounds__(kLookThreads)
 dict_lookup_kernel(const long long *__restrict__ a, int64_t n_a, const long long *__restrict__ b,
-                   int64_t n, const long long *__restrict__ sorted, Table t, const DictState *st,
-                   int *__restrict__ codes_a, int *__restrict__ codes_b) {
+                   int64_t n, const long long *__restrict__ dict, Table t,
+                   unsigned long long limit, const DictState *st, int *__restrict__ codes_a,
+                   int *__restrict__ codes_b) {
     __shared__ unsigned long long lv[kLdsSlots];
     __shared__ uint16_t lc[kLdsSlots];
-    if (st->overflow || st->count > t.max_count) return;
+    if (st->overflow || st->count > limit) return;
     const int64_t k = (int64_t)st->count;
     const int shift = st->has_min ? 1 : 0;
     const bool lds = k <= kLdsDict && n >= kLdsMinN;
@@ -354,7 +429,7 @@ dict_lookup_kernel(const long long *__restrict__ a, int64_t n_a, const long long
         for (unsigned i = threadIdx.x; i < kLdsSlots; i += kLookThreads) lv[i] = kEmpty;
         __syncthreads();
         for (int r = threadIdx.x; r < (int)k; r += kLookThreads) {
-            const unsigned long long v = (unsigned long long)sorted[r];
+            const unsigned long long v = (unsigned long long)dict[r + shift];
             // at most half of the slots are taken, so a free one is met
             unsigned h = lds_hash(v, kLdsBits);
             while (atomicCAS(lv + h, kEmpty, v) != kEmpty) h = (h + 1) & (kLdsSlots - 1);
@@ -395,60 +470,75 @@ dict_lookup_kernel(const long long *__restrict__ a, int64_t n_a, const long long
 
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 
-// Workgroups of a kernel over the columns: `per` records each, at most four of
-// 512 threads per CU (more records then take more rounds).
-constexpr int64_t kStreamWgs = 1024;
-inline unsigned stream_grid(int64_t n, int per) {
-    return (unsigned)std::min<int64_t>(kStreamWgs, (n + per - 1) / per);
+// Workgroups of a kernel over the columns: `per` records each, at most `most`
+// of 512 threads (more records then take more rounds).
+inline unsigned stream_grid(int64_t n, int per, int64_t most) {
+    return (unsigned)std::min<int64_t>(most, (n + per - 1) / per);
 }
-// columns that one value per thread covers in two rounds
-inline bool short_columns(int64_t n) { return n <= 2 * kStreamWgs * kInsThreads; }
+
+// Columns by length: one value per thread while that takes one round of 512
+// workgroups; then 512 workgroups of four (fewer meet on the same few slots at
+// the start: 10^6 values with 500 distinct 106 us in all, 116 with 1024; 10^6 +
+// 10^6 with 10^5 172 and 171); from 2^21 values 1024 of eight (2^24 + 2^24
+// values with 32 distinct 211 us, 242 with four at a time, 259 with 512
+// workgroups of four).
+constexpr int64_t kShort = (int64_t)512 * kInsThreads, kMiddle = (int64_t)1 << 21;
 
 struct Columns {
     const long long *a, *b;
     int64_t n_a, n;
 };
 
-// Steps 1-2 on one table.
-void enqueue_insert(const Columns &c, const Table &t, long long *distinct, DictState *st,
-                    hipStream_t s) {
-    const size_t slots = (size_t)t.mask + 1;
-    const size_t clear_blocks = (slots + kThreads - 1) / kThreads;
+// Steps 1-2 on one table, codes apart.
+void enqueue_insert(const Columns &c, const Table &t, unsigned int *list, DictState *st,
+                    long long *dict, hipStream_t s) {
+    const size_t clear_blocks = ((size_t)t.mask + kThreads) / kThreads;
     dict_clear_kernel<<<(unsigned)std::min<size_t>(clear_blocks, 65536), kThreads, 0, s>>>(t, st);
-    if (c.n > 0 && short_columns(c.n))
-        dict_insert_kernel<1><<<stream_grid(c.n, kInsThreads), kInsThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, t, st);
-    else if (c.n > 0)
-        dict_insert_kernel<4><<<stream_grid(c.n, kInsThreads * 4), kInsThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, t, st);
-    // slots per thread: few enough workgroups that their atomics are not the
-    // time, enough of them to fill the chip
-    if (slots <= ((size_t)1 << 20))
-        dict_compact_kernel<4><<<(unsigned)((slots + kThreads * 4 - 1) / (kThreads * 4)), kThreads,
-                                 0, s>>>(t, distinct, st);
+    if (c.n == 0) return;
+    if (c.n <= kShort)
+        dict_insert_kernel<1><<<stream_grid(c.n, kInsThreads, 512), kInsThreads, 0, s>>>(
+            c.a, c.n_a, c.b, c.n, t, list, st);
+    else if (c.n <= kMiddle)
+        dict_insert_kernel<4><<<stream_grid(c.n, kInsThreads * 4, 512), kInsThreads, 0, s>>>(
+            c.a, c.n_a, c.b, c.n, t, list, st);
     else
-        dict_compact_kernel<32><<<(unsigned)((slots + kThreads * 32 - 1) / (kThreads * 32)),
-                                  kThreads, 0, s>>>(t, distinct, st);
+        dict_insert_kernel<8><<<stream_grid(c.n, kInsThreads * 8, 1024), kInsThreads, 0, s>>>(
+            c.a, c.n_a, c.b, c.n, t, list, st);
+    dict_small_kernel<<<1, kSmallThreads, 0, s>>>(t, list, st, dict);
 }
 
-// Steps 3-4 for at most `most` distinct values.
-void enqueue_codes(const Columns &c, const Table &t, int64_t most, long long *sorted,
-                   const DictState *st, long long *dict, int *codes_a, int *codes_b,
-                   hipStream_t s) {
+void enqueue_lookup(const Columns &c, const Table &t, unsigned long long limit,
+                    const DictState *st, const long long *dict, int *codes_a, int *codes_b,
+                    hipStream_t s) {
+    if (c.n == 0) return;
+    if (c.n <= kMiddle)
+        dict_lookup_kernel<1><<<stream_grid(c.n, kLookThreads, 1024), kLookThreads, 0, s>>>(
+            c.a, c.n_a, c.b, c.n, dict, t, limit, st, codes_a, codes_b);
+    else
+        dict_lookup_kernel<8><<<stream_grid(c.n, kLookThreads * 8, 1024), kLookThreads, 0, s>>>(
+            c.a, c.n_a, c.b, c.n, dict, t, limit, st, codes_a, codes_b);
+}
+
+// Step 4 for k distinct values.
+void enqueue_codes(const Columns &c, const Table &t, int64_t k, long long *sorted, DictState *st,
+                   long long *dict, int *codes_a, int *codes_b, hipStream_t s) {
+    // slots per thread: few enough workgroups that their atomics are not the
+    // time, enough of them to fill the chip
+    const size_t slots = (size_t)t.mask + 1;
+    if (slots <= ((size_t)1 << 20))
+        dict_compact_kernel<4><<<(unsigned)((slots + kThreads * 4 - 1) / (kThreads * 4)), kThreads,
+                                 0, s>>>(t, sorted, st);
+    else
+        dict_compact_kernel<32><<<(unsigned)((slots + kThreads * 32 - 1) / (kThreads * 32)),
+                                  kThreads, 0, s>>>(t, sorted, st);
     long long *other = reinterpret_cast<long long *>(t.code);  // free until the ranks
-    if (most > 0)
-        dict_sort_runs_kernel<<<(unsigned)((most + kRunLen - 1) / kRunLen), kSortThreads, 0, s>>>(
-            sorted, other, t, st);
+    dict_sort_runs_kernel<<<(unsigned)((k + kRunLen - 1) / kRunLen), kSortThreads, 0, s>>>(
+        sorted, other, t, st);
     int64_t run = kRunLen;
-    for (int p = 0; p < merge_passes(most); ++p, run *= kFan)
-        dict_merge_kernel<<<grid_for(most), kThreads, 0, s>>>(sorted, other, run, p, t, st);
-    dict_rank_kernel<<<grid_for(most > 0 ? most : 1), kThreads, 0, s>>>(sorted, t, st, dict);
-    if (c.n > 0 && short_columns(c.n))
-        dict_lookup_kernel<1><<<stream_grid(c.n, kLookThreads), kLookThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, sorted, t, st, codes_a, codes_b);
-    else if (c.n > 0)
-        dict_lookup_kernel<4><<<stream_grid(c.n, kLookThreads * 4), kLookThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, sorted, t, st, codes_a, codes_b);
+    for (int p = 0; p < merge_passes(k); ++p, run *= kFan)
+        dict_merge_kernel<<<grid_for(k), kThreads, 0, s>>>(sorted, other, run, p, t, st);
+    dict_rank_kernel<<<grid_for(k), kThreads, 0, s>>>(sorted, t, st, dict);
+    enqueue_lookup(c, t, t.max_count, st, dict, codes_a, codes_b, s);
 }
 
 hipError_t read_state(const DictState *st, DictState *host, hipStream_t s) {
@@ -493,19 +583,13 @@ hipError_t run_dict_encode(const long long *a, int64_t n_a, const long long *b, 
         const size_t slots = attempt < 2 ? std::min(full, kSmallSlots[attempt]) : full;
         const Table t{table, slot_code, slots - 1,
                       slots == full ? (unsigned long long)full : kSmallProbes, slots / 2};
-        const int64_t most = std::min<int64_t>(c.n, (int64_t)(slots / 2));
-        enqueue_insert(c, t, sorted, st, s);
-        hipError_t e = hipSuccess;
-        if (attempt < 2) {
-            enqueue_codes(c, t, most, sorted, st, dict, codes_a, codes_b, s);
-            e = read_state(st, &host, s);
-        } else {
-            // the sort's grids and passes from the count itself
-            e = read_state(st, &host, s);
-            if (e == hipSuccess && !host.overflow && host.count <= t.max_count)
-                enqueue_codes(c, t, (int64_t)host.count, sorted, st, dict, codes_a, codes_b, s);
-        }
+        // (the list of a small dictionary takes half of the sort buffer's place)
+        enqueue_insert(c, t, reinterpret_cast<unsigned int *>(sorted), st, dict, s);
+        enqueue_lookup(c, t, kSmallDict, st, dict, codes_a, codes_b, s);
+        hipError_t e = read_state(st, &host, s);
         if (e != hipSuccess) return e;
+        if (!host.overflow && host.count <= t.max_count && host.count > kSmallDict)
+            enqueue_codes(c, t, (int64_t)host.count, sorted, st, dict, codes_a, codes_b, s);
         if (!host.overflow && host.count <= t.max_count) break;
         if (slots == full) return hipErrorUnknown;  // cannot happen by sizing
     }

@@ -16,7 +16,7 @@ I64MIN, I64MAX = np.iinfo(np.int64).min, np.iinfo(np.int64).max
 
 
 @pytest.mark.parametrize("n,distinct", [
-    (1, 1), (63, 63), (3000, 2047), (3000, 2048), (3000, 2049), (20_000, 16_384),
+    (1, 1), (63, 63), (3000, 2047), (3000, 2048), (3000, 2049), (3000, 1023), (3000, 1024), (3000, 1025), (20_000, 16_384),
     (20_000, 16_385), (131_072, 131_072), (140_000, 131_072), (140_000, 131_073),
     (600_000, 200_001), (1 << 19, 2048), (1 << 19, 2049), ((1 << 19) + 3, 7),
 ])
