@@ -440,9 +440,11 @@ tcu_status tcu_join_agg_row(const tcu_relation *A, const tcu_relation *B, int32_
  *
  * C: [M*N] FP64 row-major, every cell written (exactly 0 where no pair
  *    joins).  With A->val == NULL and B->val == NULL, C is the pair count.
- * Cost: building the tiles makes ONE host synchronisation per relation (to
- *    size the sort of its distinct tile keys), so the call blocks until the
- *    stream has reached that point.
+ * Cost: asynchronous while a bit per tile of both grids takes at most 64 MiB (and
+ *    each has at most 65536 tiles along M or N);
+ *    beyond that, building the tiles makes ONE host synchronisation per
+ *    relation (for the number of its distinct tile keys), and the call blocks
+ *    until the stream has reached that point.
  * Records out of range are skipped and counted (tcu_sync_status).
  * Duplicate cells add up (FP64 atomics) unless TCU_REL_UNIQUE_CELLS is set.
  * Workspace: tcu_join_agg_bsr_workspace_bytes(); it bounds the tile storage

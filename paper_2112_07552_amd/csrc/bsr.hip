@@ -8,20 +8,25 @@
 // tiles holding no record are never stored or multiplied, and the remaining
 // tile pairs run on the matrix cores:
 //
-//   1. tile key per record: X: (g/16, k/16), Y: (h/16, k/16), packed as
-//      outer << 32 | key tile;
-//   2. the distinct tile keys, sorted, and each record's tile index (the
-//      dictionary machinery of dict.hip: hash set, compaction, bitonic sort,
-//      rank lookup; one host synchronisation to size the sort);
-//   3. the first tile of every tile row of X and tile column of Y (binary
-//      search over the sorted keys): tile lists sorted by key tile;
+//   1. a bit per tile of X and Y, set for every record (rows of bits: tile
+//      rows of X, tile columns of Y; bit: key tile), and counted per row;
+//   2. one workgroup scans the rows' counts: the first tile of every row;
+//   3. per row, the tiles' key tiles in ascending order, the index of every
+//      64-bit word's first tile, and the tiles zeroed;
 //   4. every record's value added into its tile (16 x 16 FP64, X tiles
-//      [g%16][k%16], Y tiles [k%16][h%16]);
+//      [g%16][k%16], Y tiles [k%16][h%16]), whose index is its word's plus the
+//      bits below its own;
 //   5. per tile row of C and chunk of column tiles: the tiles whose lists
 //      share no key tile are zeroed, the others take, for every common key
 //      tile, four v_mfma_f64_16x16x4_f64 into their accumulator (see below).
 // The result equals the dense operator's: the products skipped are products
 // of all-zero tiles.  C is dense M x N FP64, as for tcu_join_agg_fwd.
+//
+// No step needs the host.  Where the bits would take more memory than the
+// dictionary machinery (kMaxBitBytes), steps 1-3 take the distinct tile keys
+// (outer << 32 | key tile) and their ranks from that, one host wait per side.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace tcu {
@@ -33,6 +38,156 @@ constexpr int kThreads = 256;
 constexpr int TB = 16;                           // tile edge
 constexpr long long kBadKey = 0x7fffffffffffffffll;  // record outside the shape
 
+// ---------------------------------------------------------- tiles by bits
+// One relation: A (outer = group of A, X) or B (outer = group of B, Y).
+struct BitSide {
+    int64_t n;
+    const int32_t *outer, *key;
+    const void *val;
+    int f32, unique, key_rows, outer_ext, rows;  // rows: outer tiles
+    unsigned long long *bits;  // rows x words
+    unsigned *word_first;      // rows x words: index of the word's first tile
+    int *ptr;                  // rows + 1
+    long long *tkeys;
+    double *tiles;
+};
+
+struct BitPair {
+    BitSide a, b;
+    int words, key_ext;
+};
+
+// The side of a launch whose workgroups [0, blocks_a) work on A; `block`
+// becomes the block's number within its side.
+__device__ inline const BitSide &bit_side(const BitPair &p, unsigned blocks_a, unsigned &block) {
+    const bool of_a = blockIdx.x < blocks_a;
+    block = of_a ? blockIdx.x : blockIdx.x - blocks_a;
+    return of_a ? p.a : p.b;
+}
+
+// Step 1.  Records outside the shape are skipped and counted here.
+__global__ void __launch_bounds__(kThreads)
+tile_bits_kernel(BitPair p, unsigned blocks_a, StatusBlock *st) {
+    unsigned block;
+    const BitSide &s = bit_side(p, blocks_a, block);
+    const int64_t i = (int64_t)block * kThreads + threadIdx.x;
+    bool bad = false;
+    if (i < s.n) {
+        const int o = s.outer[i], k = s.key[i];
+        bad = (unsigned)o >= (unsigned)s.outer_ext || (unsigned)k >= (unsigned)p.key_ext;
+        if (!bad) {
+            const int kt = k / TB;
+            unsigned long long *w = s.bits + (int64_t)(o / TB) * p.words + (kt >> 6);
+            const unsigned long long bit = 1ull << (kt & 63);
+            // a bit already set costs no atomic (one set by another XCD may
+            // still read as clear: one atomic too many)
+            if (!(__hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit))
+                atomicOr(w, bit);
+        }
+    }
+    const unsigned long long mask = __ballot(bad);
+    if (mask != 0ull && (threadIdx.x & 63) == 0) {
+        atomicOr(&st->flags, kFlagKeyRange);
+        atomicAdd(s.key_rows ? &st->skipped_b : &st->skipped_a,
+                  (unsigned long long)__popcll(mask));
+    }
+}
+
+// Each row's number of tiles, into ptr[row + 1]: one wave per row.
+__global__ void __launch_bounds__(kThreads)
+tile_count_kernel(BitPair p, unsigned blocks_a) {
+    unsigned block;
+    const BitSide &s = bit_side(p, blocks_a, block);
+    const int row = (int)block * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (row >= s.rows) return;
+    int c = 0;
+    for (int w = lane; w < p.words; w += 64) c += __popcll(s.bits[(int64_t)row * p.words + w]);
+    for (int d = 32; d > 0; d >>= 1) c += __shfl_xor(c, d);
+    if (lane == 0) s.ptr[row + 1] = c;
+}
+
+// Step 2: ptr[1 ..] from counts to their inclusive sums, ptr[0] = 0; one
+// workgroup per side.
+constexpr int kScanThreads = 1024;
+__global__ void __launch_bounds__(kScanThreads)
+tile_scan_kernel(BitPair p) {
+    __shared__ int wave_sum[kScanThreads / 64];
+    const BitSide &s = blockIdx.x == 0 ? p.a : p.b;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int before = 0;
+    if (threadIdx.x == 0) s.ptr[0] = 0;
+    for (int r0 = 0; r0 < s.rows; r0 += kScanThreads) {
+        const int r = r0 + (int)threadIdx.x;
+        int c = r < s.rows ? s.ptr[r + 1] : 0;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(c, d);
+            if (lane >= d) c += up;
+        }
+        if (lane == 63) wave_sum[wave] = c;
+        __syncthreads();
+        int base = before;
+        for (int w = 0; w < kScanThreads / 64; ++w) {
+            if (w < wave) base += wave_sum[w];
+            before += wave_sum[w];
+        }
+        if (r < s.rows) s.ptr[r + 1] = base + c;
+        __syncthreads();
+    }
+}
+
+// Step 3: one wave per row.
+__global__ void __launch_bounds__(kThreads)
+tile_list_kernel(BitPair p, unsigned blocks_a) {
+    unsigned block;
+    const BitSide &s = bit_side(p, blocks_a, block);
+    const int row = (int)block * (kThreads / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (row >= s.rows) return;
+    const int first = s.ptr[row], end = s.ptr[row + 1];
+    int at = first;
+    for (int w0 = 0; w0 < p.words; w0 += 64) {
+        const int w = w0 + lane;
+        unsigned long long bits = w < p.words ? s.bits[(int64_t)row * p.words + w] : 0ull;
+        const int c = __popcll(bits);
+        int incl = c;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int up = __shfl_up(incl, d);
+            if (lane >= d) incl += up;
+        }
+        int q = at + incl - c;
+        if (w < p.words) s.word_first[(int64_t)row * p.words + w] = (unsigned)q;
+        for (; bits; bits &= bits - 1)
+            s.tkeys[q++] = ((long long)row << 32) | (long long)(w * 64 + __builtin_ctzll(bits));
+        at += __shfl(incl, 63);
+    }
+    double2 *z = reinterpret_cast<double2 *>(s.tiles + (int64_t)first * (TB * TB));
+    const int64_t nz = (int64_t)(end - first) * (TB * TB / 2);
+    for (int64_t i = lane; i < nz; i += 64) z[i] = make_double2(0.0, 0.0);
+}
+
+// Step 4.
+__global__ void __launch_bounds__(kThreads)
+tile_place_kernel(BitPair p, unsigned blocks_a) {
+    unsigned block;
+    const BitSide &s = bit_side(p, blocks_a, block);
+    const int64_t i = (int64_t)block * kThreads + threadIdx.x;
+    if (i >= s.n) return;
+    const int o = s.outer[i], k = s.key[i];
+    if ((unsigned)o >= (unsigned)s.outer_ext || (unsigned)k >= (unsigned)p.key_ext) return;
+    const int kt = k / TB;
+    const int64_t w = (int64_t)(o / TB) * p.words + (kt >> 6);
+    const int64_t tile =
+        (int64_t)s.word_first[w] + __popcll(s.bits[w] & ((1ull << (kt & 63)) - 1ull));
+    double v = 1.0;
+    if (s.val != nullptr)
+        v = s.f32 ? (double)static_cast<const float *>(s.val)[i]
+                  : static_cast<const double *>(s.val)[i];
+    double *dst = s.tiles + tile * (TB * TB) +
+                  (s.key_rows ? (k % TB) * TB + o % TB : (o % TB) * TB + k % TB);
+    if (s.unique) *dst = v;
+    else unsafeAtomicAdd(dst, v);
+}
+
+// ---------------------------------------------------- tiles by dictionary
 template <typename T>
 __global__ void __launch_bounds__(kThreads)
 tile_key_kernel(int64_t n, const int32_t *__restrict__ outer, const int32_t *__restrict__ key,
@@ -296,9 +451,23 @@ inline int64_t max_tiles(int64_t n, int outer_ext, int key_ext) {
     return n < grid ? n : grid;
 }
 
+// Bytes of bits (both sides) up to which the tiles are found by them: the
+// bits are cleared, set, and read twice, which at this size takes about as
+// long (60 us) as the dictionary's launches and waits at any.
+constexpr int64_t kMaxBitBytes = (int64_t)64 << 20;
+// rows of bits per side that one workgroup scans, 1024 per round
+constexpr int64_t kMaxBitRows = 65536;
+
+int64_t outer_tiles(int ext) { return ((int64_t)ext + TB - 1) / TB; }
+int64_t bit_words(int K) { return (((int64_t)K + TB - 1) / TB + 63) / 64; }
+bool by_bits(int M, int K, int N) {
+    return outer_tiles(M) <= kMaxBitRows && outer_tiles(N) <= kMaxBitRows &&
+           (outer_tiles(M) + outer_tiles(N)) * bit_words(K) * 8 <= kMaxBitBytes;
+}
+
 struct Layout {
-    size_t status, dict_ws, total;
-    size_t keys[2], codes[2], tkeys[2], ptr[2], tiles[2];
+    size_t status, bits, bits_bytes, dict_ws, total;
+    size_t keys[2], codes[2], tkeys[2], ptr[2], tiles[2], side_bits[2], word_first[2];
 };
 
 Layout layout(int64_t na, int64_t nb, int M, int K, int N) {
@@ -307,23 +476,73 @@ Layout layout(int64_t na, int64_t nb, int M, int K, int N) {
     L.status = 0;
     const int64_t n[2] = {na, nb};
     const int outer[2] = {M, N};
+    const bool bits = by_bits(M, K, N);
+    if (bits) {
+        // right after the status block: both are cleared in one pass
+        L.bits = off;
+        for (int s = 0; s < 2; ++s) {
+            L.side_bits[s] = off;
+            off += (size_t)(outer_tiles(outer[s]) * bit_words(K)) * 8;
+        }
+        off = align_up(off);
+        L.bits_bytes = off - L.bits;
+        for (int s = 0; s < 2; ++s) {
+            L.word_first[s] = off;
+            off += align_up((size_t)(outer_tiles(outer[s]) * bit_words(K)) * 4);
+        }
+    }
     for (int s = 0; s < 2; ++s) {
-        L.keys[s] = off;
-        off += align_up((size_t)n[s] * 8);
-        L.codes[s] = off;
-        off += align_up((size_t)n[s] * 4);
+        if (!bits) {
+            L.keys[s] = off;
+            off += align_up((size_t)n[s] * 8);
+            L.codes[s] = off;
+            off += align_up((size_t)n[s] * 4);
+        }
         L.tkeys[s] = off;
         off += align_up((size_t)(n[s] > 0 ? n[s] : 1) * 8);
         L.ptr[s] = off;
-        off += align_up((size_t)((outer[s] + TB - 1) / TB + 1) * 4);
+        off += align_up((size_t)(outer_tiles(outer[s]) + 1) * 4);
         L.tiles[s] = off;
         off += align_up((size_t)max_tiles(n[s], outer[s], K) * TB * TB * 8);
     }
-    L.dict_ws = off;
-    const int64_t nmax = na > nb ? na : nb;
-    off += align_up(dict_workspace_bytes(nmax));
+    if (!bits) {
+        L.dict_ws = off;
+        const int64_t nmax = na > nb ? na : nb;
+        off += align_up(dict_workspace_bytes(nmax));
+    }
     L.total = off;
     return L;
+}
+
+BitSide bit_side_of(const tcu_relation &R, bool is_b, int ext, char *base, const Layout &L) {
+    const int i = is_b ? 1 : 0;
+    return BitSide{R.n, R.group, R.key, R.val, R.dtype == TCU_F32,
+                   (R.flags & TCU_REL_UNIQUE_CELLS) != 0, is_b, ext, (int)outer_tiles(ext),
+                   reinterpret_cast<unsigned long long *>(base + L.side_bits[i]),
+                   reinterpret_cast<unsigned *>(base + L.word_first[i]),
+                   reinterpret_cast<int *>(base + L.ptr[i]),
+                   reinterpret_cast<long long *>(base + L.tkeys[i]),
+                   reinterpret_cast<double *>(base + L.tiles[i])};
+}
+
+// Steps 1-4 of both relations by bits, the status block cleared.
+hipError_t build_by_bits(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                         char *base, const Layout &L, StatusBlock *st, hipStream_t s) {
+    const BitPair p{bit_side_of(A, false, M, base, L), bit_side_of(B, true, N, base, L),
+                    (int)bit_words(K), K};
+    hipError_t e = launch_zero_f64(reinterpret_cast<double *>(st),
+                                   (L.bits + L.bits_bytes) / sizeof(double), s);
+    if (e != hipSuccess) return e;
+    const unsigned ga = grid_for(A.n), gb = grid_for(B.n);
+    constexpr unsigned kRows = kThreads / 64;
+    const unsigned ra = ((unsigned)p.a.rows + kRows - 1) / kRows;
+    const unsigned rb = ((unsigned)p.b.rows + kRows - 1) / kRows;
+    if (ga + gb > 0) tile_bits_kernel<<<ga + gb, kThreads, 0, s>>>(p, ga, st);
+    tile_count_kernel<<<ra + rb, kThreads, 0, s>>>(p, ra);
+    tile_scan_kernel<<<2, kScanThreads, 0, s>>>(p);
+    tile_list_kernel<<<ra + rb, kThreads, 0, s>>>(p, ra);
+    if (ga + gb > 0) tile_place_kernel<<<ga + gb, kThreads, 0, s>>>(p, ga);
+    return hipGetLastError();
 }
 
 template <typename T>
@@ -341,7 +560,6 @@ hipError_t scatter_t(const tcu_relation &R, const Side &sd, int key_rows, hipStr
 // Steps 1-4 for one relation: outer = group column (g for A, h for B).
 hipError_t build_side(const tcu_relation &R, int outer_ext, int K, int which, const Side &sd,
                       void *dict_ws, StatusBlock *st, hipStream_t s) {
-    const int outer_tiles = (outer_ext + TB - 1) / TB;
     int64_t ntiles = 0;
     if (R.n > 0) {
         if (R.dtype == TCU_F32)
@@ -365,8 +583,8 @@ hipError_t build_side(const tcu_relation &R, int outer_ext, int K, int which, co
                                : scatter_t<double>(R, sd, which, s);
         if (e != hipSuccess) return e;
     }
-    tile_ptr_kernel<<<grid_for(outer_tiles + 1), kThreads, 0, s>>>(sd.tkeys, ntiles, outer_tiles,
-                                                                   sd.ptr);
+    const int ot = (int)outer_tiles(outer_ext);
+    tile_ptr_kernel<<<grid_for(ot + 1), kThreads, 0, s>>>(sd.tkeys, ntiles, ot, sd.ptr);
     return hipGetLastError();
 }
 
@@ -389,11 +607,14 @@ hipError_t run_join_agg_bsr(const tcu_relation &A, const tcu_relation &B, int M,
         sd[i].ptr = reinterpret_cast<int *>(base + L.ptr[i]);
         sd[i].tiles = reinterpret_cast<double *>(base + L.tiles[i]);
     }
-    hipError_t e = launch_clear_status(st, s);
-    if (e != hipSuccess) return e;
-    e = build_side(A, M, K, 0, sd[0], base + L.dict_ws, st, s);
-    if (e != hipSuccess) return e;
-    e = build_side(B, N, K, 1, sd[1], base + L.dict_ws, st, s);
+    hipError_t e;
+    if (L.bits_bytes > 0) {
+        e = build_by_bits(A, B, M, K, N, base, L, st, s);
+    } else {
+        e = launch_clear_status(st, s);
+        if (e == hipSuccess) e = build_side(A, M, K, 0, sd[0], base + L.dict_ws, st, s);
+        if (e == hipSuccess) e = build_side(B, N, K, 1, sd[1], base + L.dict_ws, st, s);
+    }
     if (e != hipSuccess) return e;
     const int mt = (M + TB - 1) / TB, nt = (N + TB - 1) / TB;
     // wide chunks share the row's keys and give long stores; fewer column
