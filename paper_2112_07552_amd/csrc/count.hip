@@ -13,6 +13,7 @@ namespace tcu {
 namespace {
 
 typedef int i4 __attribute__((ext_vector_type(4)));
+typedef double d2 __attribute__((ext_vector_type(2)));
 typedef int i16v __attribute__((ext_vector_type(16)));
 
 constexpr int kThreads = 256;
@@ -64,12 +65,17 @@ count_planes_kernel(int64_t na, const int32_t *__restrict__ ga, const int32_t *_
 // wave), one k-step ahead.  Workgroups take the tiles in row-major order, so
 // that those in flight write long runs of the same rows: 377 us (5.7 TB/s; a
 // plain fill reaches 6.7) against 438 us in the GEMMs' order of eight
-// tile rows per XCD, and 504 us for the FP64 product.  A result larger than
+// tile rows per XCD, and 504 us for the FP64 product (these with 8-byte stores).  A result larger than
 // the last-level cache goes past the caches (NT), which then keep the planes:
 // 33024 x 4096 cells over 512 keys 217 us against 334 us, FP64 2067 us; at
 // 4096 x 4096 cells, which a next kernel may still find cached, it would gain
 // nothing (127 and 130 us over 4096 keys, FP64 1959 us).
-template <bool NT>
+// A lane's two columns of a wave's 64 are neighbours (column block b holds the
+// columns 2 l + b), so that a wave stores 512 bytes of a row per instruction
+// (PAIR: an even n and aligned outputs; 8 bytes per store otherwise):
+// 16384 x 16384 cells over 32 keys 360 us instead of 368, 33024 x 4096 over 512
+// 175 instead of 194.
+template <bool NT, bool PAIR>
 __global__ void __launch_bounds__(kThreads)
 count_product_kernel(int m, int n, int nblk, int tiles_n,
                      const int8_t *__restrict__ xs, int xlp, const int8_t *__restrict__ ys,
@@ -83,7 +89,7 @@ count_product_kernel(int m, int n, int nblk, int tiles_n,
     const int l32 = lane & 31, half = lane >> 5;
     const int r0 = m0 + (wave & 1) * 64, c0 = n0 + (wave >> 1) * 64;
     const int8_t *xp = xs + ((int64_t)half * xlp + r0 + l32) * 16;
-    const int8_t *yp = ys + ((int64_t)half * ylp + c0 + l32) * 16;
+    const int8_t *yp = ys + ((int64_t)half * ylp + c0 + 2 * l32) * 16;
     const int64_t xstep = (int64_t)xlp * 32, ystep = (int64_t)ylp * 32;
 
     i16v acc[2][2];
@@ -95,7 +101,7 @@ count_product_kernel(int m, int n, int nblk, int tiles_n,
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
         xa[a] = *reinterpret_cast<const i4 *>(xp + a * 512);
-        yb[a] = *reinterpret_cast<const i4 *>(yp + a * 512);
+        yb[a] = *reinterpret_cast<const i4 *>(yp + a * 16);
     }
     for (int kb = 0; kb < nblk; ++kb) {
         // the last k-step loads itself again
@@ -107,7 +113,7 @@ count_product_kernel(int m, int n, int nblk, int tiles_n,
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
             xn[a] = *reinterpret_cast<const i4 *>(xp + a * 512);
-            yn[a] = *reinterpret_cast<const i4 *>(yp + a * 512);
+            yn[a] = *reinterpret_cast<const i4 *>(yp + a * 16);
         }
 #pragma unroll
         for (int a = 0; a < 2; ++a)
@@ -126,17 +132,32 @@ count_product_kernel(int m, int n, int nblk, int tiles_n,
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int row = r0 + a * 32 + 8 * (i >> 2) + 4 * half + (i & 3);
-            if (row >= m) continue;
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const int col = c0 + b * 32 + l32;
-                if (col >= n) continue;
-                if (C != nullptr) {
-                    double *dst = C + (int64_t)row * ldc + col;
-                    if (NT) __builtin_nontemporal_store((double)acc[a][b][i], dst);
-                    else *dst = (double)acc[a][b][i];
+            const int col = c0 + 2 * l32;
+            if (row >= m || col >= n) continue;
+            const int v0 = acc[a][0][i], v1 = acc[a][1][i];
+            if (C != nullptr) {
+                double *dst = C + (int64_t)row * ldc + col;
+                if (PAIR) {
+                    if (NT) __builtin_nontemporal_store(d2{(double)v0, (double)v1},
+                                                        reinterpret_cast<d2 *>(dst));
+                    else *reinterpret_cast<d2 *>(dst) = d2{(double)v0, (double)v1};
+                } else {
+                    if (NT) __builtin_nontemporal_store((double)v0, dst);
+                    else *dst = (double)v0;
+                    if (col + 1 < n) {
+                        if (NT) __builtin_nontemporal_store((double)v1, dst + 1);
+                        else dst[1] = (double)v1;
+                    }
                 }
-                if (cnt != nullptr) cnt[(int64_t)row * ldcnt + col] = acc[a][b][i];
+            }
+            if (cnt != nullptr) {
+                int32_t *dst = cnt + (int64_t)row * ldcnt + col;
+                if (PAIR) {
+                    *reinterpret_cast<int2 *>(dst) = make_int2(v0, v1);
+                } else {
+                    *dst = v0;
+                    if (col + 1 < n) dst[1] = v1;
+                }
             }
         }
 }
@@ -172,12 +193,12 @@ hipError_t launch_count_planes_product(int M, int K, int N, const int8_t *qa, co
     TraceScope ts(TCU_KERNEL_COUNT, M, N, K, 1, 2.0 * M * N * (double)K, s);
     const int tiles_n = blp / BN, nblk = (K + 31) / 32;
     const unsigned grid = (unsigned)((int64_t)(alp / BM) * tiles_n);
-    if ((size_t)M * (size_t)N * sizeof(double) > kLastLevelCache)
-        count_product_kernel<true><<<grid, kThreads, 0, s>>>(M, N, nblk, tiles_n, qa, alp, qb, blp,
-                                                             C, N, cnt, N);
-    else
-        count_product_kernel<false><<<grid, kThreads, 0, s>>>(M, N, nblk, tiles_n, qa, alp, qb,
-                                                              blp, C, N, cnt, N);
+    const bool nt = (size_t)M * (size_t)N * sizeof(double) > kLastLevelCache;
+    const bool pair = N % 2 == 0 && ((uintptr_t)C & 15) == 0 && ((uintptr_t)cnt & 7) == 0;
+    auto *kernel = nt ? (pair ? count_product_kernel<true, true> : count_product_kernel<true, false>)
+                      : (pair ? count_product_kernel<false, true>
+                              : count_product_kernel<false, false>);
+    kernel<<<grid, kThreads, 0, s>>>(M, N, nblk, tiles_n, qa, alp, qb, blp, C, N, cnt, N);
     return hipGetLastError();
 }
 
