@@ -50,6 +50,7 @@ struct BitSide {
     int *ptr;                  // rows + 1
     long long *tkeys;
     double *tiles;
+    unsigned *mask;  // per tile: the keys (mod 16) that have a record; NULL: not wanted
 };
 
 struct BitPair {
@@ -159,6 +160,8 @@ tile_list_kernel(BitPair p, unsigned blocks_a) {
             s.tkeys[q++] = ((long long)row << 32) | (long long)(w * 64 + __builtin_ctzll(bits));
         at += __shfl(incl, 63);
     }
+    if (s.mask != nullptr)
+        for (int i = first + lane; i < end; i += 64) s.mask[i] = 0u;
     double2 *z = reinterpret_cast<double2 *>(s.tiles + (int64_t)first * (TB * TB));
     const int64_t nz = (int64_t)(end - first) * (TB * TB / 2);
     for (int64_t i = lane; i < nz; i += 64) z[i] = make_double2(0.0, 0.0);
@@ -185,6 +188,7 @@ tile_place_kernel(BitPair p, unsigned blocks_a) {
                   (s.key_rows ? (k % TB) * TB + o % TB : (o % TB) * TB + k % TB);
     if (s.unique) *dst = v;
     else unsafeAtomicAdd(dst, v);
+    if (s.mask != nullptr) atomicOr(s.mask + tile, 1u << (k % TB));
 }
 
 // ---------------------------------------------------- tiles by dictionary
@@ -246,27 +250,40 @@ tile_scatter_kernel(int64_t n, const int32_t *__restrict__ outer, const int32_t 
 // what costs is finding out.  One wave per tile, walking both key lists one
 // scalar load after the other, took 1555 us on 1024 x 1024 tiles of which
 // 256 meet (2.1 GB of zeros, 1.4 TB/s).  Here a workgroup takes one tile row
-// of C and up to kMaxChunk column tiles:
+// of C and kChunk column tiles:
 //   1. the row's X keys go to LDS, as a list and as a bit per key modulo
-//      8192, and each thread tests one column tile: a short list of Y against
+//      8192, and eight threads test one column tile: a short list of Y against
 //      the bits and, where one is set, by binary search of the list (a short
 //      list of X against a long one of Y by searches in the latter; lists
 //      that both exceed kTestKeys keys are taken to meet);
-//   2. the tiles that do not meet are zeroed row by row in long stores;
+//   2. the tiles that do not meet are zeroed row by row, past the caches when
+//      C exceeds the last-level one;
 //   3. the others go to the waves, one tile each: the lanes take 64 keys of
 //      the shorter list, search the longer, and the tile pairs that meet run
 //      on the matrix cores in ascending key order (as the serial walk did, so
 //      the sums round the same).
-// The same product then takes about 450 us (4.7 TB/s of stores; a plain fill
-// reaches 6.7); 4096 x 4096 cells where nine tiles in ten meet 285 us for the
-// whole operator against 707, a graph's 65536 x 64 with long lists of Y 324
-// against 2751.
-constexpr int kMaxChunk = 256;   // column tiles per workgroup, one per thread
-constexpr int kMinChunk = 32;
+// For pair counts (no values on either side) two tiles also have to share a
+// key, by a mask of 16 keys per tile, to meet: with one record per tile, one
+// pair in 16 does.  (With values a zero of one tile may meet an infinity of
+// the other, so every pair of tiles counts.)
+// At 16384^2 cells the operator then takes 379-424 us with 1000 to 2^20 distinct
+// keys (C alone: 377 at 5.7 TB/s; without the masks and with cached stores 1992
+// with 1000, 473 with 2^20); 4096 x 4096 cells where nine tiles in ten meet 285
+// us against 707 by serial walks, a graph's 65536 x 64 with long lists of Y
+// 324 against 2751 (both before the tiles were found by bits).
+// Column tiles per workgroup.  At 16384^2 cells (us of the operator for 4000 and
+// 2^20 distinct keys, one thread per column tile): 32 tiles 407 and 414, 64 tiles
+// 416 and 430, 256 tiles 445 and 450; with cached stores 578 and 420, 494 and
+// 427, 519 and 441.
+constexpr int kChunk = 32;
+constexpr int kTesters = kThreads / kChunk;  // threads per column tile
+constexpr size_t kLastLevelCache = (size_t)256 << 20;
+constexpr int kPastCaches = 2;  // 16-byte stores past the caches (1: through them; 0: 8-byte)
+typedef double d2 __attribute__((ext_vector_type(2)));
 constexpr int kXKeys = 1024;     // X keys of one tile row held in LDS
 constexpr int kTestKeys = 64;
 constexpr int kBits = 8192;      // one bit per key modulo this: set for the row's X keys
-static_assert(kMaxChunk == kThreads, "one thread per column tile");
+static_assert(kThreads % kChunk == 0 && 64 % kTesters == 0, "testers of a tile share a wave");
 
 __device__ inline int key_of(int k) { return k; }
 __device__ inline int key_of(long long k) { return (int)(k & 0xffffffffll); }
@@ -299,16 +316,28 @@ __device__ inline void load_pair(const double *xt, const double *yt, int64_t xi,
     }
 }
 
+// Whether X tile `at` of the row (its mask in LDS) and the list's Y tile y, or
+// the X tile of mask m and Y tile `at`, share a key; at < 0: no such tile.
+__device__ inline bool shares(int at, const uint16_t *xm, int y, const unsigned *ym) {
+    return at >= 0 && (ym == nullptr || (xm[at] & ym[y]) != 0u);
+}
+__device__ inline bool shares_at(unsigned m, int at, const unsigned *ym) {
+    return at >= 0 && (ym == nullptr || (m & ym[at]) != 0u);
+}
+
 __global__ void __launch_bounds__(kThreads)
-bsr_product_kernel(int M, int N, int nt, int chunk, const long long *__restrict__ xkeys,
+bsr_product_kernel(int M, int N, int nt, const long long *__restrict__ xkeys,
                    const int *__restrict__ xptr, const double *__restrict__ xt,
                    const long long *__restrict__ ykeys, const int *__restrict__ yptr,
-                   const double *__restrict__ yt, double *__restrict__ C, int64_t ldc, int vec) {
+                   const double *__restrict__ yt, const unsigned *__restrict__ xmask,
+                   const unsigned *__restrict__ ymask, double *__restrict__ C, int64_t ldc,
+                   int vec) {
     __shared__ int xk[kXKeys];
+    __shared__ uint16_t xm[kXKeys];
     __shared__ unsigned bits[kBits / 32];
-    __shared__ unsigned char meets[kMaxChunk];
-    const int gt = blockIdx.y, h0 = blockIdx.x * chunk;
-    const int cols = min(chunk, nt - h0);  // column tiles of this workgroup
+    __shared__ unsigned char meets[kChunk];
+    const int gt = blockIdx.y, h0 = blockIdx.x * kChunk;
+    const int cols = min(kChunk, nt - h0);  // column tiles of this workgroup
     const int t = threadIdx.x, lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int xa = xptr[gt], nx = xptr[gt + 1] - xa;
@@ -320,31 +349,36 @@ bsr_product_kernel(int M, int N, int nt, int chunk, const long long *__restrict_
         for (int i = t; i < nx; i += kThreads) {
             const int key = key_of(xlist[i]);
             xk[i] = key;
+            xm[i] = xmask != nullptr ? (uint16_t)xmask[xa + i] : (uint16_t)0xffff;
             atomicOr(bits + (key / 32) % (kBits / 32), 1u << (key % 32));
         }
     __syncthreads();
 
-    if (t < cols) {
-        const int ya = yptr[h0 + t], ny = yptr[h0 + t + 1] - ya;
-        const long long *ylist = ykeys + ya;
-        bool meet = min(nx, ny) > kTestKeys;
-        if (!meet && ny <= kTestKeys && in_lds) {
-            for (int i0 = 0; i0 < ny && !meet; i0 += 8) {
-                int key[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) key[i] = key_of(ylist[min(i0 + i, ny - 1)]);
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    if (!meet && (bits[(key[i] / 32) % (kBits / 32)] >> (key[i] % 32) & 1u))
-                        meet = find_key(xk, nx, key[i]) >= 0;
+    {
+        const int b = t / kTesters, part = t % kTesters;
+        bool meet = false;
+        if (b < cols) {
+            const int ya = yptr[h0 + b], ny = yptr[h0 + b + 1] - ya;
+            const long long *ylist = ykeys + ya;
+            const unsigned *ym = ymask != nullptr ? ymask + ya : nullptr;
+            meet = min(nx, ny) > kTestKeys;
+            if (!meet && ny <= kTestKeys && in_lds) {
+                for (int i = part; i < ny && !meet; i += kTesters) {
+                    const int key = key_of(ylist[i]);
+                    if (bits[(key / 32) % (kBits / 32)] >> (key % 32) & 1u)
+                        meet = shares(find_key(xk, nx, key), xm, i, ym);
+                }
+            } else if (!meet && nx <= kTestKeys) {
+                for (int i = part; i < nx && !meet; i += kTesters)
+                    meet = shares_at(xm[i], find_key(ylist, ny, xk[i]), ym);
+            } else if (!meet) {
+                for (int i = part; i < ny && !meet; i += kTesters)
+                    meet = find_key(xlist, nx, key_of(ylist[i])) >= 0;
             }
-        } else if (!meet && nx <= kTestKeys) {
-            for (int i = 0; i < nx && !meet; ++i) meet = find_key(ylist, ny, xk[i]) >= 0;
-        } else if (!meet) {
-            for (int i = 0; i < ny && !meet; ++i)
-                meet = find_key(xlist, nx, key_of(ylist[i])) >= 0;
         }
-        meets[t] = meet;
+        const unsigned long long any = __ballot(meet);
+        const unsigned long long group = ((1ull << kTesters) - 1ull) << (lane & ~(kTesters - 1));
+        if (part == 0 && b < cols) meets[b] = (any & group) != 0ull;
     }
     __syncthreads();
 
@@ -354,18 +388,20 @@ bsr_product_kernel(int M, int N, int nt, int chunk, const long long *__restrict_
     double *Crow = C + (int64_t)gt * TB * ldc;
     // (row by row, so that the workgroup's stores run along each row of C)
     if (vec) {
-        // columns c0 + 2 t + 512 p; N is even: a pair never straddles the edge
-        constexpr int kPasses = kMaxChunk * TB / (2 * kThreads);
-        unsigned todo = 0;
-        for (int p = 0; p < kPasses; ++p) {
-            const int c = 2 * t + 2 * kThreads * p;
-            if (c0 + c < cend && !meets[c / TB]) todo |= 1u << p;
-        }
-        for (int r = 0; r < rows; ++r) {
-            double2 *dst = reinterpret_cast<double2 *>(Crow + r * ldc + c0) + t;
-#pragma unroll
-            for (int p = 0; p < kPasses; ++p)
-                if (todo >> p & 1) dst[p * kThreads] = make_double2(0.0, 0.0);
+        // two columns per thread; N is even: a pair never straddles the edge
+        static_assert(kChunk * TB == 2 * kThreads, "one pair of columns per thread");
+        if (c0 + 2 * t < cend && !meets[2 * t / TB]) {
+            double *dst = Crow + c0 + 2 * t;
+            // (two loops: as the two sides of one branch the stores are
+            // merged into a cached one)
+            if (vec == kPastCaches) {
+                for (int r = 0; r < rows; ++r)
+                    __builtin_nontemporal_store(d2{0.0, 0.0},
+                                                reinterpret_cast<d2 *>(dst + r * ldc));
+            } else {
+                for (int r = 0; r < rows; ++r)
+                    *reinterpret_cast<d2 *>(dst + r * ldc) = d2{0.0, 0.0};
+            }
         }
     } else {
         for (int r = 0; r < rows; ++r)
@@ -398,6 +434,7 @@ bsr_product_kernel(int M, int N, int nt, int chunk, const long long *__restrict_
                     yi = s;
                 }
             }
+            if (at >= 0 && in_lds && ymask != nullptr && (xm[xi] & ymask[ya + yi]) == 0u) at = -1;
             unsigned long long mask = __ballot(at >= 0);
             while (mask) {
                 // two pairs at a time: the second one's loads are in flight
@@ -467,7 +504,7 @@ bool by_bits(int M, int K, int N) {
 
 struct Layout {
     size_t status, bits, bits_bytes, dict_ws, total;
-    size_t keys[2], codes[2], tkeys[2], ptr[2], tiles[2], side_bits[2], word_first[2];
+    size_t keys[2], codes[2], tkeys[2], ptr[2], tiles[2], side_bits[2], word_first[2], mask[2];
 };
 
 Layout layout(int64_t na, int64_t nb, int M, int K, int N) {
@@ -497,6 +534,9 @@ Layout layout(int64_t na, int64_t nb, int M, int K, int N) {
             off += align_up((size_t)n[s] * 8);
             L.codes[s] = off;
             off += align_up((size_t)n[s] * 4);
+        } else {
+            L.mask[s] = off;
+            off += align_up((size_t)n[s] * 4);
         }
         L.tkeys[s] = off;
         off += align_up((size_t)(n[s] > 0 ? n[s] : 1) * 8);
@@ -514,7 +554,8 @@ Layout layout(int64_t na, int64_t nb, int M, int K, int N) {
     return L;
 }
 
-BitSide bit_side_of(const tcu_relation &R, bool is_b, int ext, char *base, const Layout &L) {
+BitSide bit_side_of(const tcu_relation &R, bool is_b, int ext, bool masks, char *base,
+                    const Layout &L) {
     const int i = is_b ? 1 : 0;
     return BitSide{R.n, R.group, R.key, R.val, R.dtype == TCU_F32,
                    (R.flags & TCU_REL_UNIQUE_CELLS) != 0, is_b, ext, (int)outer_tiles(ext),
@@ -522,14 +563,16 @@ BitSide bit_side_of(const tcu_relation &R, bool is_b, int ext, char *base, const
                    reinterpret_cast<unsigned *>(base + L.word_first[i]),
                    reinterpret_cast<int *>(base + L.ptr[i]),
                    reinterpret_cast<long long *>(base + L.tkeys[i]),
-                   reinterpret_cast<double *>(base + L.tiles[i])};
+                   reinterpret_cast<double *>(base + L.tiles[i]),
+                   masks ? reinterpret_cast<unsigned *>(base + L.mask[i]) : nullptr};
 }
 
 // Steps 1-4 of both relations by bits, the status block cleared.
 hipError_t build_by_bits(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
-                         char *base, const Layout &L, StatusBlock *st, hipStream_t s) {
-    const BitPair p{bit_side_of(A, false, M, base, L), bit_side_of(B, true, N, base, L),
-                    (int)bit_words(K), K};
+                         bool masks, char *base, const Layout &L, StatusBlock *st,
+                         hipStream_t s) {
+    const BitPair p{bit_side_of(A, false, M, masks, base, L),
+                    bit_side_of(B, true, N, masks, base, L), (int)bit_words(K), K};
     hipError_t e = launch_zero_f64(reinterpret_cast<double *>(st),
                                    (L.bits + L.bits_bytes) / sizeof(double), s);
     if (e != hipSuccess) return e;
@@ -608,8 +651,9 @@ hipError_t run_join_agg_bsr(const tcu_relation &A, const tcu_relation &B, int M,
         sd[i].tiles = reinterpret_cast<double *>(base + L.tiles[i]);
     }
     hipError_t e;
+    const bool masks = L.bits_bytes > 0 && A.val == nullptr && B.val == nullptr;
     if (L.bits_bytes > 0) {
-        e = build_by_bits(A, B, M, K, N, base, L, st, s);
+        e = build_by_bits(A, B, M, K, N, masks, base, L, st, s);
     } else {
         e = launch_clear_status(st, s);
         if (e == hipSuccess) e = build_side(A, M, K, 0, sd[0], base + L.dict_ws, st, s);
@@ -617,19 +661,16 @@ hipError_t run_join_agg_bsr(const tcu_relation &A, const tcu_relation &B, int M,
     }
     if (e != hipSuccess) return e;
     const int mt = (M + TB - 1) / TB, nt = (N + TB - 1) / TB;
-    // wide chunks share the row's keys and give long stores; fewer column
-    // tiles per workgroup while the grid has fewer than 16384 of them (about
-    // nine rounds): measured at 16384^2 cells, 2^20 keys, 726 us for the
-    // operator with at least 4096 workgroups, 706 with 8192, 682 with 16384
-    int chunk = kMaxChunk;
-    while (chunk > kMinChunk && (int64_t)mt * ((nt + chunk - 1) / chunk) < 16384) chunk /= 2;
-    const int vec = N % 2 == 0 && ((uintptr_t)C & 15) == 0;
+    const int vec = N % 2 != 0 || ((uintptr_t)C & 15) != 0 ? 0
+                    : (size_t)M * (size_t)N * sizeof(double) > kLastLevelCache ? kPastCaches : 1;
     for (int g0 = 0; g0 < mt; g0 += 65535) {
         // tile rows run along the grid's y, at most 65535 per launch
         const int gn = mt - g0 < 65535 ? mt - g0 : 65535;
-        bsr_product_kernel<<<dim3((unsigned)((nt + chunk - 1) / chunk), (unsigned)gn), kThreads, 0,
-                             s>>>(M - g0 * TB, N, nt, chunk, sd[0].tkeys, sd[0].ptr + g0,
+        bsr_product_kernel<<<dim3((unsigned)((nt + kChunk - 1) / kChunk), (unsigned)gn), kThreads, 0,
+                             s>>>(M - g0 * TB, N, nt, sd[0].tkeys, sd[0].ptr + g0,
                                   sd[0].tiles, sd[1].tkeys, sd[1].ptr, sd[1].tiles,
+                                  masks ? reinterpret_cast<unsigned *>(base + L.mask[0]) : nullptr,
+                                  masks ? reinterpret_cast<unsigned *>(base + L.mask[1]) : nullptr,
                                   C + (int64_t)g0 * TB * N, N, vec);
     }
     return hipGetLastError();
