@@ -423,8 +423,11 @@ tcu_status tcu_dict_encode(const int64_t *a, int64_t n_a, const int64_t *b, int6
  * [0,K) (or a B group outside [0,N)) are skipped and counted in the status
  * block at the start of ws (tcu_sync_status).  Floating-point sums use
  * atomics (order-dependent last bits); counts are exact.  ws: at least
- * tcu_join_agg_row_workspace_bytes(K, N) bytes, 256-byte aligned. */
+ * tcu_join_agg_row_workspace_bytes(K, N) bytes, 256-byte aligned; with
+ * tcu_join_agg_row_scratch_bytes(A, K) more (0 for short tables or few keys) a
+ * long table of many keys is summed in LDS instead of by global atomics. */
 size_t tcu_join_agg_row_workspace_bytes(int32_t K, int32_t N);
+size_t tcu_join_agg_row_scratch_bytes(const tcu_relation *A, int32_t K);
 tcu_status tcu_join_agg_row(const tcu_relation *A, const tcu_relation *B, int32_t K, int32_t N,
                             double *c, uint64_t *count, void *ws, size_t ws_bytes,
                             hipStream_t stream);

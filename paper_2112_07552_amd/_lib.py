@@ -50,7 +50,7 @@ EXPORTS = (
     "tcu_encode_workspace_bytes", "tcu_gemm_f64",
     "tcu_gemm_f64_workspace_bytes", "tcu_gemm_f64_ws",
     "tcu_join_agg_fwd", "tcu_join_agg_fwd_noalloc", "tcu_join_agg_bwd", "tcu_dict_workspace_bytes", "tcu_dict_encode",
-    "tcu_join_agg_row_workspace_bytes", "tcu_join_agg_row",
+    "tcu_join_agg_row_workspace_bytes", "tcu_join_agg_row_scratch_bytes", "tcu_join_agg_row",
     "tcu_join_agg_bsr_workspace_bytes", "tcu_join_agg_bsr", "tcu_block_sparse_preferred",
     "tcu_nonzero_workspace_bytes",
     "tcu_nonzero", "tcu_gemm_f64_host", "tcu_mfma_peak_out_bytes", "tcu_mfma_peak_ops",
@@ -139,6 +139,8 @@ def load():
     L.tcu_dict_encode.restype = C.c_int
     L.tcu_join_agg_row_workspace_bytes.argtypes = [i32, i32]
     L.tcu_join_agg_row_workspace_bytes.restype = C.c_size_t
+    L.tcu_join_agg_row_scratch_bytes.argtypes = [rel_p, i32]
+    L.tcu_join_agg_row_scratch_bytes.restype = C.c_size_t
     L.tcu_join_agg_row.argtypes = [rel_p, rel_p, i32, i32, vp, vp, vp, C.c_size_t, vp]
     L.tcu_join_agg_row.restype = C.c_int
     L.tcu_join_agg_bsr_workspace_bytes.argtypes = [rel_p, rel_p, i32, i32, i32]

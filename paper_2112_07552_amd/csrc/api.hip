@@ -1006,6 +1006,11 @@ size_t tcu_join_agg_row_workspace_bytes(int32_t K, int32_t N) {
     return row_workspace_bytes(K, N);
 }
 
+size_t tcu_join_agg_row_scratch_bytes(const tcu_relation *A, int32_t K) {
+    if (!relation_ok(A) || K < 1) return 0;
+    return row_scratch_bytes(*A, K);
+}
+
 tcu_status tcu_join_agg_row(const tcu_relation *A, const tcu_relation *B, int32_t K, int32_t N,
                             double *c, uint64_t *count, void *ws, size_t ws_bytes,
                             hipStream_t stream) {
@@ -1013,7 +1018,7 @@ tcu_status tcu_join_agg_row(const tcu_relation *A, const tcu_relation *B, int32_
     if (!ws_ok(ws, ws_bytes, row_workspace_bytes(K, N))) return TCU_ERR_WORKSPACE;
     return hip_status(run_join_agg_row(*A, *B, K, N, c,
                                        reinterpret_cast<unsigned long long *>(count), ws,
-                                       stream));
+                                       ws_bytes, stream));
 }
 
 size_t tcu_join_agg_bsr_workspace_bytes(const tcu_relation *A, const tcu_relation *B,

@@ -35,7 +35,7 @@ constexpr int kMaxCells = 8192;          // cells per tile
 // them side by side.
 struct Side {
     int64_t n;
-    const int32_t *row, *col;
+    const int32_t *row, *col;  // row NULL: one row, number 0
     const void *val;
     int f32;
     int rows, cols;
@@ -59,7 +59,7 @@ __device__ inline const Side &side_of(const Both &p, int64_t per, int &chunk) {
 }
 
 __device__ inline bool tile_of(const Side &s, int64_t i, int &tile, unsigned &cell) {
-    const int r = s.row[i], c = s.col[i];
+    const int r = s.row != nullptr ? s.row[i] : 0, c = s.col[i];
     if ((unsigned)r >= (unsigned)s.rows || (unsigned)c >= (unsigned)s.cols) return false;
     tile = (r >> s.lr) * s.across + (c >> s.lc);
     cell = ((unsigned)(r & ((1 << s.lr) - 1)) << s.lc) | (unsigned)(c & ((1 << s.lc) - 1));
@@ -259,6 +259,34 @@ bin_fill_kernel(Both p, const uint32_t *__restrict__ offsets, const uint16_t *__
     }
 }
 
+// Step 4 of a histogram over keys (one row of cells): sums and numbers of
+// records.
+__global__ void __launch_bounds__(kThreads)
+bin_hist_kernel(Side s, const uint32_t *__restrict__ offsets, const uint16_t *__restrict__ cell,
+                const double *__restrict__ val, unsigned long long *__restrict__ counts) {
+    __shared__ double v[kMaxCells];
+    __shared__ unsigned c[kMaxCells];
+    const int cells = 1 << s.lc, t = threadIdx.x;
+    const int64_t c0 = (int64_t)blockIdx.x << s.lc;
+    for (int i = t; i < cells; i += kThreads) {
+        v[i] = 0.0;
+        c[i] = 0u;
+    }
+    __syncthreads();
+    const uint32_t lo = offsets[blockIdx.x], hi = offsets[blockIdx.x + 1];
+    for (uint32_t q = lo + t; q < hi; q += kThreads) {
+        const unsigned i = cell[q];
+        atomicAdd(&v[i], val[q]);
+        atomicAdd(&c[i], 1u);
+    }
+    __syncthreads();
+    for (int i = t; i < cells; i += kThreads)
+        if (c0 + i < s.cols) {
+            s.out[c0 + i] = v[i];
+            counts[c0 + i] = c[i];
+        }
+}
+
 struct TilePlan {
     int lr = 5, lc = 8, across = 0, tiles = 0;
 };
@@ -348,6 +376,24 @@ Scratch scratch_layout(const Plan &p, int64_t n) {
     return w;
 }
 
+// Tiles of one row of K cells: at least 512 of them where K has 16 times that.
+TilePlan hist_plan(int K) {
+    TilePlan p;
+    p.lr = 0;
+    p.lc = 4;
+    while ((1 << p.lc) < kMaxCells && ((int64_t)K >> p.lc) >= 1024) ++p.lc;
+    const int64_t across = ((int64_t)K + (1 << p.lc) - 1) >> p.lc;
+    if (across > kMaxTiles) return TilePlan{};
+    p.across = p.tiles = (int)across;
+    return p;
+}
+
+// Records from which the histogram's tiles pay (us of the whole of Q3 with as
+// many records on both sides, 500 groups, 3000 and 400000 keys; two global
+// atomics per record against these launches): 2^18 46 and 55 against 35 and 56,
+// 2^19 75 and 80 against 38 and 59, 2^24 1910 and 1679 against 333 and 479.
+constexpr int64_t kMinHistRecords = (int64_t)1 << 18;
+
 Side make_side(const tcu_relation &R, bool is_b, const TilePlan &t, int rows, int cols, int first,
                double *out, int8_t *plane, int lines_pad, int len_pad) {
     return Side{R.n, is_b ? R.key : R.group, is_b ? R.group : R.key, R.val, R.dtype == TCU_F32,
@@ -355,7 +401,52 @@ Side make_side(const tcu_relation &R, bool is_b, const TilePlan &t, int rows, in
                 len_pad};
 }
 
+// Steps 1-3.
+hipError_t partition(const Both &both, int tiles, const Scratch &w, char *base, StatusBlock *st,
+                     hipStream_t s) {
+    auto *totals = reinterpret_cast<uint32_t *>(base + w.totals);
+    auto *cursor = reinterpret_cast<uint32_t *>(base + w.cursor);
+    auto chunks = [&](int64_t per) {
+        return (unsigned)((both.a.n + per - 1) / per + (both.b.n + per - 1) / per);
+    };
+    const hipError_t e = launch_zero_f64(reinterpret_cast<double *>(totals),
+                                         align_up((size_t)(tiles + 1) * 4) / 8, s);
+    if (e != hipSuccess) return e;
+    bin_count_kernel<<<chunks(kHistChunk), kThreads, 0, s>>>(both, totals, st);
+    bin_offsets_kernel<<<1, kThreads, 0, s>>>(
+        totals, reinterpret_cast<uint32_t *>(base + w.offsets), cursor, tiles);
+    bin_partition_kernel<<<chunks(kChunk), kThreads, 0, s>>>(
+        both, cursor, reinterpret_cast<uint16_t *>(base + w.cell),
+        reinterpret_cast<double *>(base + w.val));
+    return hipGetLastError();
+}
+
 }  // namespace
+
+size_t binned_hist_scratch_bytes(const tcu_relation &A, int K) {
+    Plan p;
+    if (A.n < kMinHistRecords || A.n > 0x7fffffffLL) return 0;
+    p.a = hist_plan(K);
+    return p.a.tiles > 0 ? scratch_layout(p, A.n).bytes : 0;
+}
+
+hipError_t launch_binned_hist(const tcu_relation &A, int K, double *h, unsigned long long *hc,
+                              StatusBlock *st, void *scratch, hipStream_t s) {
+    Plan p;
+    p.a = hist_plan(K);
+    if (p.a.tiles == 0 || A.n < 1) return hipErrorInvalidValue;
+    const Scratch w = scratch_layout(p, A.n);
+    char *base = static_cast<char *>(scratch);
+    Both both{};
+    both.a = Side{A.n, nullptr, A.key, A.val, A.dtype == TCU_F32, 1, K, p.a.lr, p.a.lc,
+                  p.a.across, p.a.tiles, 0, h, nullptr, 0, 0, 0};
+    const hipError_t e = partition(both, p.a.tiles, w, base, st, s);
+    if (e != hipSuccess) return e;
+    bin_hist_kernel<<<(unsigned)p.a.tiles, kThreads, 0, s>>>(
+        both.a, reinterpret_cast<uint32_t *>(base + w.offsets),
+        reinterpret_cast<uint16_t *>(base + w.cell), reinterpret_cast<double *>(base + w.val), hc);
+    return hipGetLastError();
+}
 
 size_t binned_scratch_bytes(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
                             bool planes) {
@@ -371,8 +462,6 @@ hipError_t launch_binned(const tcu_relation &A, const tcu_relation &B, int M, in
     if (!make_plan(A, B, M, K, N, planes, &p)) return hipErrorInvalidValue;
     const Scratch w = scratch_layout(p, A.n + B.n);
     char *base = static_cast<char *>(scratch);
-    auto *totals = reinterpret_cast<uint32_t *>(base + w.totals);
-    auto *cursor = reinterpret_cast<uint32_t *>(base + w.cursor);
     auto *offsets = reinterpret_cast<uint32_t *>(base + w.offsets);
     auto *qa = reinterpret_cast<int8_t *>(base + w.qa), *qb = reinterpret_cast<int8_t *>(base + w.qb);
     auto *cell = reinterpret_cast<uint16_t *>(base + w.cell);
@@ -380,13 +469,8 @@ hipError_t launch_binned(const tcu_relation &A, const tcu_relation &B, int M, in
     Both both{make_side(A, false, p.a, M, K, 0, X, planes ? qa : nullptr, p.alp, p.len),
               make_side(B, true, p.b, K, N, p.a.tiles, Y, planes ? qb : nullptr, p.blp, p.len)};
     const int tiles = p.a.tiles + p.b.tiles;
-    auto chunks = [&](int64_t per) { return (unsigned)((A.n + per - 1) / per + (B.n + per - 1) / per); };
-    hipError_t e = launch_zero_f64(reinterpret_cast<double *>(totals),
-                                   align_up((size_t)(tiles + 1) * 4) / 8, s);
+    hipError_t e = partition(both, tiles, w, base, st, s);
     if (e != hipSuccess) return e;
-    bin_count_kernel<<<chunks(kHistChunk), kThreads, 0, s>>>(both, totals, st);
-    bin_offsets_kernel<<<1, kThreads, 0, s>>>(totals, offsets, cursor, tiles);
-    bin_partition_kernel<<<chunks(kChunk), kThreads, 0, s>>>(both, cursor, cell, val);
     if (!planes) {
         bin_fill_kernel<kSums><<<(unsigned)tiles, kThreads, 0, s>>>(both, offsets, cell, val, st,
                                                                     nullptr);

@@ -204,6 +204,13 @@ hipError_t launch_binned(const tcu_relation &A, const tcu_relation &B, int M, in
                          double *X, double *Y, int32_t *count, double *C, StatusBlock *st,
                          void *scratch, hipStream_t s);
 
+// The histogram of Q3 over K keys by the same means: h[k] = sum of A's values,
+// hc[k] = number of A's records with key k (A's group column is not read).
+// scratch: binned_hist_scratch_bytes (0: not taken), 256-byte aligned.
+size_t binned_hist_scratch_bytes(const tcu_relation &A, int K);
+hipError_t launch_binned_hist(const tcu_relation &A, int K, double *h, unsigned long long *hc,
+                              StatusBlock *st, void *scratch, hipStream_t s);
+
 // dict.hip: dictionary encoding (ranks in the sorted union of two columns).
 size_t dict_workspace_bytes(int64_t n);
 hipError_t run_dict_encode(const long long *a, int64_t n_a, const long long *b, int64_t n_b,
@@ -212,9 +219,12 @@ hipError_t run_dict_encode(const long long *a, int64_t n_a, const long long *b, 
 
 // reassoc.hip: Q3/Q4 in re-associated form (histogram of A by key, then one
 // pass over B grouped by B's group column).
+// A workspace with row_scratch_bytes more lets long tables of many keys sort
+// their records into tiles (binned.hip).
 size_t row_workspace_bytes(int K, int N);
-hipError_t run_join_agg_row(const tcu_relation &A, const tcu_relation &B, int K, int N,
-                            double *c, unsigned long long *count, void *ws, hipStream_t s);
+size_t row_scratch_bytes(const tcu_relation &A, int K);
+hipError_t run_join_agg_row(const tcu_relation &A, const tcu_relation &B, int K, int N, double *c,
+                            unsigned long long *count, void *ws, size_t ws_bytes, hipStream_t s);
 
 // bsr.hip: the join-aggregate on 16 x 16 block-sparse encodings (tiles
 // without records skipped); C dense M x N FP64.

@@ -20,9 +20,11 @@
 // order.  One copy per workgroup and global atomics at its end took 101 and 96
 // us for 2^24 records with 32 keys and 32 groups, 48 and 40 now (4.2 and 3.4
 // TB/s of the columns) and 9 for each table; 10^6 records in 500 groups, where
-// the atomics were the time, 51 and now 15 + 5.  Larger arrays take FP64 atomics in
-// global memory directly; such sums, and those in LDS, are order-dependent at
-// the last bits; counts are exact.
+// the atomics were the time, 51 and now 15 + 5.  More keys
+// than that are summed tile by tile (binned.hip) when the workspace has the
+// scratch; else, and for more groups, FP64 atomics go to global memory
+// directly.  Such sums, and those in LDS, are order-dependent at the last
+// bits; counts are exact.
 #include <algorithm>
 
 #include "internal.h"
@@ -290,8 +292,12 @@ size_t row_workspace_bytes(int K, int N) {
            align_up((size_t)N * 8) + align_up(std::max(table_bytes(K), table_bytes(N)));
 }
 
-hipError_t run_join_agg_row(const tcu_relation &A, const tcu_relation &B, int K, int N,
-                            double *c, unsigned long long *count, void *ws, hipStream_t s) {
+size_t row_scratch_bytes(const tcu_relation &A, int K) {
+    return K > kLdsBins ? binned_hist_scratch_bytes(A, K) : 0;
+}
+
+hipError_t run_join_agg_row(const tcu_relation &A, const tcu_relation &B, int K, int N, double *c,
+                            unsigned long long *count, void *ws, size_t ws_bytes, hipStream_t s) {
     char *p = static_cast<char *>(ws);
     StatusBlock *st = reinterpret_cast<StatusBlock *>(p);
     p += sizeof(StatusBlock);
@@ -303,8 +309,12 @@ hipError_t run_join_agg_row(const tcu_relation &A, const tcu_relation &B, int K,
     p += align_up((size_t)N * 8);
     hipError_t e = launch_clear_status(st, s);
     if (e != hipSuccess) return e;
-    e = A.dtype == TCU_F32 ? hist_t<float>(A, K, h, hc, p, st, s)
-                           : hist_t<double>(A, K, h, hc, p, st, s);
+    const size_t base = row_workspace_bytes(K, N), bin = row_scratch_bytes(A, K);
+    if (bin > 0 && ws_bytes >= base + bin)
+        e = launch_binned_hist(A, K, h, hc, st, static_cast<char *>(ws) + base, s);
+    else
+        e = A.dtype == TCU_F32 ? hist_t<float>(A, K, h, hc, p, st, s)
+                               : hist_t<double>(A, K, h, hc, p, st, s);
     if (e != hipSuccess) return e;
     return B.dtype == TCU_F32 ? group_t<float>(B, K, N, h, hc, c, cnt, p, st, s)
                               : group_t<double>(B, K, N, h, hc, c, cnt, p, st, s);

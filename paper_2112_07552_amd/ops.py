@@ -304,11 +304,13 @@ def join_agg_row(a_key, a_val, b_key, b_group, b_val, K: int, N: int, with_count
     dev = a_key.device
     A = make_relation(a_key, a_key, a_val)  # the group column is not read
     B = make_relation(b_group, b_key, b_val)
-    ws = alloc_workspace(int(_lib.load().tcu_join_agg_row_workspace_bytes(K, N)), dev)
+    L = _lib.load()
+    ws = alloc_workspace(int(L.tcu_join_agg_row_workspace_bytes(K, N)) +
+                         int(L.tcu_join_agg_row_scratch_bytes(C.byref(A), K)), dev)
     c = torch.empty(N, dtype=torch.float64, device=dev)
     cnt = torch.empty(N, dtype=torch.int64, device=dev) if with_count else None
-    check(_lib.load().tcu_join_agg_row(C.byref(A), C.byref(B), K, N, _ptr(c), _ptr(cnt),
-                                       _ptr(ws), ws.numel(), _stream(dev)), "tcu_join_agg_row")
+    check(L.tcu_join_agg_row(C.byref(A), C.byref(B), K, N, _ptr(c), _ptr(cnt),
+                             _ptr(ws), ws.numel(), _stream(dev)), "tcu_join_agg_row")
     return c, cnt, ws
 
 
