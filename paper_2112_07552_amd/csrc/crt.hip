@@ -340,23 +340,19 @@ mag_cols_kernel(const double *__restrict__ Z, int rows, int cols, int64_t ld,
 // The same sums bound the integer product from above: with |z| 2^(7 - e) = q +
 // f, 0 <= f < 1, each term (q_x + f_x)(q_y + f_y) is at most q_x q_y + 128
 // (|x| 2^-e + |y| 2^-f'), so 2^14 times the normalised (|X||Y|)[g,h] is at most
-// T + 128 (s_g + s_h), and at most 2^14 min(s_g, s_h), as every normalised
-// value is below 1.  The largest of these over the cells (rounded to float;
-// the plan adds 2^-20) is what the modulus product has to hold: 2^3.4 against
+// T + 128 (s_g + s_h).  The largest of these over the cells (rounded to float;
+// the plan adds 2^-20), or the line sums' bound where that is less, is what the modulus product has to hold: 2^3.4 against
 // 2^7.3 by the line sums alone at 4096^3 log-uniform values, where 13 moduli
 // then do for 14; 2^2.8 against 2^7.6 at 16384^3 of the outlier mixture, 14 for
 // 15.
-// The residue form's need of one cell: the smallest b >= 1 with r <= 2^b u,
-// u = tcrt T, read off the exponents and mantissas of r (enlarged past the
-// rounding of u) and u: with r = mr 2^er and u = mu 2^eu (mantissas in
-// [0.5, 1)), b = er - eu, plus 1 when mr > mu.
-__device__ inline uint32_t cert_bits(double r, int T, const CertArgs &ca) {
-    if (T <= 0) return r > 0.0 ? kNeedUncertified : 0u;
-    if (r <= 0.0) return 0u;
-    int er, eu;
-    const double mr = frexp(r * (1.0 + 0x1p-40), &er);
-    const double mu = frexp(ca.tcrt * (double)T, &eu);
-    const int b = er - eu + (mr > mu ? 1 : 0);
+// The residue form's need of one cell with T > 0: the smallest b >= 1 with r <=
+// 2^b u, u = tcrt T, for r enlarged past the rounding of u.  As 64-bit integers
+// the encodings of two positive normal doubles differ by 2^52 times the
+// difference of their exponents plus that of their mantissas, so b is the
+// difference over 2^52, rounded up.
+__device__ inline uint32_t cert_bits(double r_up, int T, const CertArgs &ca) {
+    const long long d = __double_as_longlong(r_up) - __double_as_longlong(ca.tcrt * (double)T);
+    const int b = (int)((d + 0xfffffffffffffll) >> 52);
     return (uint32_t)min(max(b, 1), (int)kNeedUncertified - 1);
 }
 
@@ -699,6 +695,19 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
         // residues' order: one 16-byte store per lane and 32 x 32 block), and
         // the largest and the smallest nonzero need among the cells the
         // certificate bounds.
+        // The tile's line sums come from LDS, free once every wave has left the
+        // main loop (read from memory cell by cell, and with the needs by frexp,
+        // the certificate of a 4096^3 product took 113 us, 86 now; the
+        // products alone are about 58).  Rows and columns past the edge count as
+        // all-zero lines, which make every term of their cells zero in the exact
+        // and in the truncated product alike.
+        __syncthreads();
+        double *sums = reinterpret_cast<double *>(lds);
+        for (int i = threadIdx.x; i < G::BM + G::BN; i += G::threads) {
+            const int row = m0 + i, col = n0 + i - G::BM;
+            sums[i] = i < G::BM ? (row < m ? ca.sx[row] : 0.0) : (col < n ? ca.sy[col] : 0.0);
+        }
+        __syncthreads();
         uint32_t need = 0, cneed = 0, mneed = kNeedUncertified;
         float ucell = 0.0f;
 #pragma unroll
@@ -709,25 +718,29 @@ gemm_crt_kernel(int m, int n, int nblk, int tiles_m, int tiles_n, const int8_t *
             for (int b = 0; b < WB; ++b) {
                 const int col = n0 + wn * 32 * WB + b * 32 + l32;
                 if (col >= n) continue;
-                const double sy = ca.sy[col];
+                const double sy = sums[G::BM + col - n0];
                 uint32_t w[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int row = rbase + 8 * (i >> 2) + 4 * half + (i & 3);
-                    if (row >= m) continue;
-                    // an all-zero line makes every term of the cell zero
-                    // in the exact and in the truncated product alike
-                    const double sx = ca.sx[row];
-                    const double r = (sx > 0.0 && sy > 0.0) ? 16384.0 * (sx + sy) : 0.0;
-                    const uint32_t c = EPI == kEpiCertify ? cert_bits(r, acc[a][b][i], ca)
-                                                          : cert_slices(r, acc[a][b][i], ca);
-                    if (EPI == kEpiCertify && r > 0.0)
-                        ucell = fmaxf(ucell, fminf(fmaf((float)r, 0x1p-7f, (float)acc[a][b][i]),
-                                                   16384.0f * (float)fmin(sx, sy)));
+                    const double sx = sums[rbase - m0 + 8 * (i >> 2) + 4 * half + (i & 3)];
+                    const int T = acc[a][b][i];
+                    const bool zero = !(sx > 0.0) || !(sy > 0.0);
+                    const double s = sx + sy;
+                    uint32_t c;
+                    if (EPI == kEpiCertify)
+                        c = T > 0 ? cert_bits(s * (16384.0 * (1.0 + 0x1p-40)), T, ca)
+                                  : kNeedUncertified;
+                    else
+                        c = cert_slices(16384.0 * s, T, ca);
+                    if (zero) c = 0u;
+                    if (EPI == kEpiCertify && !zero)
+                        ucell = fmaxf(ucell, fmaf((float)s, 128.0f, (float)T));
                     need = max(need, c);
                     if (c < kNeedUncertified) cneed = max(cneed, c);
                     if (c > 0) mneed = min(mneed, c);
                     w[i >> 2] |= c << (8 * (i & 3));
+                    // (more cells at once would spill beside the sums)
+                    if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);
                 }
                 if (EPI == kEpiCertify && ca.need_plane != nullptr)
                     *reinterpret_cast<uint4 *>(ca.need_plane +
