@@ -897,6 +897,13 @@ tcu_status tcu_join_agg_bwd(const tcu_relation *A, const tcu_relation *B, int32_
     // dX and dY live in separate buffers (G, G2), so nothing the two streams
     // run at the same time touches the same memory.
     const bool both = dA_val != nullptr && dB_val != nullptr;
+    if (both && !mixed && gather_pair_fits(*A, *B) && (saved || encode_pair_fits(M, K, N))) {
+        // short tables: one stream, one scatter, one gather
+        if (!saved) TCU_TRY(launch_encode_pair(*A, *B, M, K, N, X, Y, st, stream));
+        TCU_TRY(launch_gemm_f64_split(0, 1, M, K, N, dC, N, Y, N, G, K, split_part(ws, L), stream));
+        TCU_TRY(launch_gemm_f64_split(1, 0, K, N, M, X, K, dC, N, G2, N, split_part(ws, L), stream));
+        return hip_status(launch_gather_pair(*A, *B, M, K, N, G, G2, dA_val, dB_val, stream));
+    }
     hipStream_t side = nullptr;
     CallEvents evs;
     if (both) {

@@ -149,6 +149,21 @@ gather_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restr
     dst[i] = valid ? src[(size_t)r * (size_t)cols + c] : 0.0;
 }
 
+// Both relations' gathers in one launch (workgroups as encode_pair_kernel):
+// dst[i] = out[row_i, col_i], 0 for records outside the matrix.
+__global__ void __launch_bounds__(kThreads)
+gather_pair_kernel(PairSide a, PairSide b, unsigned blocks_a, double *__restrict__ da,
+                   double *__restrict__ db) {
+    const bool of_a = blockIdx.x < blocks_a;
+    const PairSide &p = of_a ? a : b;
+    double *dst = of_a ? da : db;
+    const int64_t i = (int64_t)(of_a ? blockIdx.x : blockIdx.x - blocks_a) * kThreads + threadIdx.x;
+    if (i >= p.n) return;
+    const int r = p.row[i], c = p.col[i];
+    const bool valid = (unsigned)r < (unsigned)p.rows && (unsigned)c < (unsigned)p.cols;
+    dst[i] = valid ? p.out[(size_t)r * (size_t)p.cols + c] : 0.0;
+}
+
 // ------------------------------------------------------- windowed scatter
 // Random 8-byte stores into a matrix far larger than the last-level cache run
 // at about a third of the rate they reach when the matrix stays cached (2^30
@@ -381,6 +396,12 @@ f64_to_i32_kernel(const double *__restrict__ src, int32_t *__restrict__ dst, siz
 // hold them.
 constexpr size_t kPairBytes = (size_t)64 << 20;
 
+// Records per relation up to which the adjoint gathers both gradients in one
+// launch at its end (us of a whole FP64 step, one stream and two): 256^3 152 and
+// 174-212 (the host's time), 1024^3 207 and 203-219, 1448^3 535 and 530, 2048^3
+// 1227 and 1210.
+constexpr int64_t kPairRecords = (int64_t)1 << 20;
+
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 
 inline unsigned capped_grid(size_t n) {
@@ -466,6 +487,21 @@ hipError_t launch_encode_pair(const tcu_relation &A, const tcu_relation &B, int 
                      (B.flags & TCU_REL_UNIQUE_CELLS) != 0, K, N, Y};
     const unsigned ga = grid_for(A.n);
     encode_pair_kernel<<<ga + grid_for(B.n), kThreads, 0, s>>>(a, b, ga, st);
+    return hipGetLastError();
+}
+
+bool gather_pair_fits(const tcu_relation &A, const tcu_relation &B) {
+    return A.n <= kPairRecords && B.n <= kPairRecords;
+}
+
+hipError_t launch_gather_pair(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                              double *dX, double *dY, double *dA, double *dB, hipStream_t s) {
+    if (A.n + B.n == 0) return hipSuccess;
+    TraceScope ts(TCU_KERNEL_GATHER, M, N, K, 2, ((double)A.n + (double)B.n) * 24.0, s);
+    const PairSide a{A.n, A.group, A.key, nullptr, 0, 0, M, K, dX};
+    const PairSide b{B.n, B.key, B.group, nullptr, 0, 0, K, N, dY};
+    const unsigned ga = grid_for(A.n);
+    gather_pair_kernel<<<ga + grid_for(B.n), kThreads, 0, s>>>(a, b, ga, dA, dB);
     return hipGetLastError();
 }
 

@@ -117,6 +117,11 @@ hipError_t launch_encode_zeroed(const tcu_relation &R, int transpose, int rows, 
 bool encode_pair_fits(int M, int K, int N);
 hipError_t launch_encode_pair(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
                               double *X, double *Y, StatusBlock *st, hipStream_t s);
+// Both gathers of the adjoint in one launch, for tables so short that a second
+// stream's events cost more than its overlap gains.
+bool gather_pair_fits(const tcu_relation &A, const tcu_relation &B);
+hipError_t launch_gather_pair(const tcu_relation &A, const tcu_relation &B, int M, int K, int N,
+                              double *dX, double *dY, double *dA, double *dB, hipStream_t s);
 // dst[i] = src[row_i, col_i] for the records whose row lies in [r0, r1)
 // (r1 < 0: all rows); the launch with r0 = 0 also writes 0 for records
 // outside the matrix.
