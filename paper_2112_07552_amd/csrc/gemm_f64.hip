@@ -11,19 +11,21 @@
 //    gfx950: rows interleave with stride 4 across the lane groups).
 //  * Workgroup tile 128 x 128, 4 waves in a 2 x 2 grid, each wave owning a
 //    64 x 64 block (4 x 4 MFMA blocks, 64 FP64 accumulators per lane).
-//  * K advances in stages of 16 through double-buffered LDS; global loads of
-//    stage s+1 are issued before the MFMAs of stage s and written to the other
-//    buffer afterwards, so one barrier per stage suffices.
+//  * K advances in stages of 16 through double-buffered LDS, one barrier per
+//    stage.  Everything but the MFMAs is issued between them, one item after
+//    each (64 cycles): the next k-step's fragments, stage s + 1's global loads
+//    (k-step 0) and their LDS stores (k-step 2); see full_stage.  With the loads
+//    and each k-step's fragment reads in front of its MFMAs instead, 4096^3 took
+//    1940 us (70.8 TFLOP/s) and 2048^3 309; now 1867 (73.6, NT and TN 74.2) and
+//    278.  The kernel stays within 128 VGPRs + 128 AGPRs, so two workgroups (two
+//    waves per SIMD) share a CU and cover each other's barriers.
 //  * Inside a stage, lane group j = lane/16 at k-step t (0..3) contracts
-//    k = 4j + t (any bijection of the 16 k values is a valid contraction
-//    order as long as A and B use the same one).  Fragments are read from LDS
-//    one k-step at a time, which keeps the kernel within 128 VGPRs + 128
-//    AGPRs, so two workgroups (two waves per SIMD) share a CU and cover each
-//    other's barrier and load stalls.
+//    k = 4t + j (any bijection of the 16 k values is a valid contraction
+//    order as long as A and B use the same one).
 //  * Operands whose contraction index is contiguous in memory are staged as
-//    [outer][16 + 2] in LDS, the others as [16][128 + 2]; the pads spread rows
-//    over the LDS banks.  Global loads are 16-byte vectors when the leading
-//    dimension and base address allow, 8-byte guarded loads otherwise.
+//    [outer][16 + 2] in LDS, the others as [16][128 + 16]: with these pads the
+//    32 lanes that LDS serves together read 64 different banks.  Global loads
+//    are 16-byte vectors at any 8-byte alignment.
 //  * Tiles are numbered so that each of the 8 XCDs (workgroup w runs on XCD
 //    w mod 8) owns a contiguous run of tiles, grouped 8 tile-rows deep, so
 //    the A and B panels a run needs stay in that XCD's L2.
@@ -52,7 +54,7 @@ constexpr int THREADS = 256;
 constexpr int WM = 64, WN = 64;
 constexpr int FM = WM / 16, FN = WN / 16;
 constexpr int KPAD = BK + 2;    // row stride of a contraction-contiguous tile
-constexpr int OPAD = 128 + 2;   // row stride of an outer-contiguous tile
+constexpr int OPAD = 128 + 16;  // row stride of an outer-contiguous tile
 constexpr int GROUP_M = 8;
 constexpr int NUM_XCD = 8;
 
@@ -61,30 +63,21 @@ struct Tile {
     static constexpr int elems = KC ? 128 * KPAD : BK * OPAD;
 };
 
+// Chunk i of a thread (2 doubles) to its place in an LDS tile.
 template <bool KC>
-__device__ inline void store_tile(double *__restrict__ L, const double2 (&r)[4]) {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int c = tid + THREADS * i;
-        int off;
-        if (KC) off = (c >> 3) * KPAD + (c & 7) * 2;
-        else    off = (c >> 6) * OPAD + (c & 63) * 2;
-        *reinterpret_cast<double2 *>(L + off) = r[i];
-    }
+__device__ __forceinline__ void store_chunk(double *__restrict__ L, int i, double2 v) {
+    const int c = threadIdx.x + THREADS * i;
+    const int off = KC ? (c >> 3) * KPAD + (c & 7) * 2 : (c >> 6) * OPAD + (c & 63) * 2;
+    *reinterpret_cast<double2 *>(L + off) = v;
 }
 
-// Fragments of k-step t of one stage: f[block] = the lane's element of
-// MFMA block `block` (row or column wbase + 16*block + lane%16, k = 4j + t).
-template <bool KC, int F>
-__device__ inline void read_frags(const double *__restrict__ L, int wbase, int t, double (&f)[F]) {
+// The lane's element of MFMA block b in k-step t of a stage: row or column
+// wbase + 16 b + lane % 16, k = 4 t + lane / 16.
+template <bool KC>
+__device__ __forceinline__ double read_frag(const double *__restrict__ L, int wbase, int t, int b) {
     const int lane = threadIdx.x & 63;
-    const int j = lane >> 4, l16 = lane & 15;
-#pragma unroll
-    for (int b = 0; b < F; ++b) {
-        const int o = wbase + b * 16 + l16;
-        f[b] = KC ? L[o * KPAD + 4 * j + t] : L[(4 * j + t) * OPAD + o];
-    }
+    const int o = wbase + b * 16 + (lane & 15), k = 4 * t + (lane >> 4);
+    return KC ? L[o * KPAD + k] : L[k * OPAD + o];
 }
 
 // ----- tile path: no vector-ALU work in the main loop.  While the matrix
@@ -133,58 +126,60 @@ __device__ __forceinline__ Panel make_panel(const double *P, int64_t ld, int o0)
     return q;
 }
 
-__device__ __forceinline__ void load_panel(const Panel &q, int kt, double2 (&r)[4]) {
-    gchar *b = q.base + (int64_t)kt * q.step;
+// Chunk i of stage kt.
+__device__ __forceinline__ double2 load_chunk(const Panel &q, int kt, int i) {
+    gchar *bi = q.base + (int64_t)kt * q.step + i * q.istep;
+    asm volatile("" : "+s"(bi));  // keep the chunk's base a scalar operand
     // Redefine the offset here so its zero extension is not hoisted out of
     // the loop: the SGPR-base + 32-bit-offset load form needs to see it.
     unsigned off = q.off;
     asm volatile("" : "+v"(off));
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        // a native vector load (a HIP double2 copied from the global address
-        // space would go through private memory)
-        gchar *bi = b + i * q.istep;
-        asm volatile("" : "+s"(bi));  // keep the chunk's base a scalar operand
-        const d2v v = *reinterpret_cast<gd2v *>(bi + off);
-        r[i].x = v.x;
-        r[i].y = v.y;
-    }
+    // a native vector load (a HIP double2 copied from the global address
+    // space would go through private memory)
+    const d2v v = *reinterpret_cast<gd2v *>(bi + off);
+    return make_double2(v.x, v.y);
 }
 
-// One stage of the tile loop reading LDS buffer CUR: loads of stage
-// kt + 1 (the last stage reloads itself into the idle buffer), 3 k-steps of
-// MFMAs, the loaded tiles stored to buffer CUR ^ 1, the last k-step, a
-// barrier.
+struct Frags {
+    double a[FM], b[FN];
+};
+
+// One stage of the tile loop on LDS buffer CUR, whose k-step 0 is in f0
+// already: while the 16 MFMAs of a k-step run, one after the other, the next
+// k-step's fragments are read, stage kt + 1's chunks are loaded (k-step 0) and
+// stored to buffer CUR ^ 1 (k-step 2); the workgroup meets before the last
+// k-step, which then reads stage kt + 1's k-step 0.  No wave reads buffer
+// CUR ^ 1 between the previous stage's meeting and this one's.  (The last stage
+// loads itself again, into a buffer that is not multiplied any more.)
 template <bool A_KC, bool B_KC, int CUR>
 __device__ __forceinline__ void full_stage(int kt, int nk, const Panel &pa, const Panel &pb,
-                                  double (*lds_a)[Tile<A_KC>::elems],
-                                  double (*lds_b)[Tile<B_KC>::elems], int wm, int wn,
-                                  d4 (&acc)[FM][FN]) {
-    double2 ra[4], rb[4];
+                                           double (*lds_a)[Tile<A_KC>::elems],
+                                           double (*lds_b)[Tile<B_KC>::elems], int wm, int wn,
+                                           Frags &f0, d4 (&acc)[FM][FN]) {
+    static_assert(FM * FN >= FM + FN && FM * FN >= 8, "one read or load per MFMA");
+    double2 r[8];
     const int knext = kt + 1 < nk ? kt + 1 : kt;
-    load_panel(pa, knext, ra);
-    load_panel(pb, knext, rb);
-    __builtin_amdgcn_sched_barrier(0);
+    Frags f = f0;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
-        // No wave reads buffer CUR ^ 1 during this stage (all passed the
-        // previous barrier), so the loaded tiles go there before the last
-        // k-step, whose MFMAs then cover the LDS writes.
-        if (t == 3) {
-            store_tile<A_KC>(lds_a[CUR ^ 1], ra);
-            store_tile<B_KC>(lds_b[CUR ^ 1], rb);
+        if (t == 3) __syncthreads();
+        const double *la = lds_a[t == 3 ? CUR ^ 1 : CUR], *lb = lds_b[t == 3 ? CUR ^ 1 : CUR];
+        Frags g;
+#pragma unroll
+        for (int i = 0; i < FM * FN; ++i) {
+            acc[i / FN][i % FN] = __builtin_amdgcn_mfma_f64_16x16x4f64(
+                f.a[i / FN], f.b[i % FN], acc[i / FN][i % FN], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (i < FM) g.a[i] = read_frag<A_KC>(la, wm * WM, (t + 1) % 4, i);
+            else if (i < FM + FN) g.b[i - FM] = read_frag<B_KC>(lb, wn * WN, (t + 1) % 4, i - FM);
+            if (t == 0 && i < 8) r[i] = i < 4 ? load_chunk(pa, knext, i) : load_chunk(pb, knext, i - 4);
+            if (t == 2 && i < 4) store_chunk<A_KC>(lds_a[CUR ^ 1], i, r[i]);
+            else if (t == 2 && i < 8) store_chunk<B_KC>(lds_b[CUR ^ 1], i - 4, r[i]);
             __builtin_amdgcn_sched_barrier(0);
         }
-        double fa[FM], fb[FN];
-        read_frags<A_KC, FM>(lds_a[CUR], wm * WM, t, fa);
-        read_frags<B_KC, FN>(lds_b[CUR], wn * WN, t, fb);
-#pragma unroll
-        for (int a = 0; a < FM; ++a)
-#pragma unroll
-            for (int b = 0; b < FN; ++b)
-                acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
+        f = g;
     }
-    __syncthreads();
+    f0 = f;
 }
 
 template <int TILE_M, int TILE_N>
@@ -237,16 +232,28 @@ gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
     const Panel pa = make_panel<A_KC>(A, lda, m0);
     const Panel pb = make_panel<B_KC>(B, ldb, n0);
     {
-        double2 ra[4], rb[4];
-        load_panel(pa, 0, ra);
-        load_panel(pb, 0, rb);
-        store_tile<A_KC>(lds_a[0], ra);
-        store_tile<B_KC>(lds_b[0], rb);
+        double2 r[8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            r[i] = load_chunk(pa, 0, i);
+            r[i + 4] = load_chunk(pb, 0, i);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            store_chunk<A_KC>(lds_a[0], i, r[i]);
+            store_chunk<B_KC>(lds_b[0], i, r[i + 4]);
+        }
     }
     __syncthreads();
+    Frags f0;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) f0.a[i] = read_frag<A_KC>(lds_a[0], wm * WM, 0, i);
+#pragma unroll
+    for (int i = 0; i < FN; ++i) f0.b[i] = read_frag<B_KC>(lds_b[0], wn * WN, 0, i);
     for (int kt = 0; kt < nk; kt += 2) {
-        full_stage<A_KC, B_KC, 0>(kt, nk, pa, pb, lds_a, lds_b, wm, wn, acc);
-        if (kt + 1 < nk) full_stage<A_KC, B_KC, 1>(kt + 1, nk, pa, pb, lds_a, lds_b, wm, wn, acc);
+        full_stage<A_KC, B_KC, 0>(kt, nk, pa, pb, lds_a, lds_b, wm, wn, f0, acc);
+        if (kt + 1 < nk)
+            full_stage<A_KC, B_KC, 1>(kt + 1, nk, pa, pb, lds_a, lds_b, wm, wn, f0, acc);
     }
     // the last k % 16 terms, lane group j's term of step t at k = 4 t + j
     for (int kk = nk * BK; kk < k; kk += 4) {
@@ -505,18 +512,18 @@ enum Kernel { kTile, kDirectWide, kDirectSmall };  // 128 x 128; 32 x 64; 32 x 3
 // (two per CU of the first two, four of the last), then the rest with w
 // workgroups per CU, at a share of the CU's 0.307 TFLOP/s that grows with w,
 // plus the launch with its first loads and last stores.  The shares are fits
-// to measured products (us; tile, 32 x 64, 32 x 32): 512^3 71, 13, 8.3;
-// 1024^3 60, 38, 42; 2048^3 309, 262, 332; 4096^3 1930, 1998, -; 1500 x 2777
-// x 2051 (264 tiles) 487, 304, 343.  The direct kernels read both operands of
-// A B^T in 64-byte pieces of many rows, which costs them more (1500 x 2051 x
-// 2777: 340, not 304; 4096^3: 2770).
+// to measured products (us, many in a row; tile, 32 x 64, 32 x 32): 512^3 -, 13,
+// 8.4; 1024^3 126, 43, 45; 2048^3 278, 306, 332; 4096^3 1867, 1998, -; 1500 x
+// 2777 x 2051 (264 tiles) 478, 336, 342; 3000^3 1030, 846, -.  The direct kernels
+// read both operands of A B^T in 64-byte pieces of many rows, which costs them
+// more (2048^3: 368, the tile kernel 265).
 double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus) {
     struct Shape {
         int bm, bn, per_cu;
         double one, full, fixed;
     };
-    const Shape sh = which == kTile         ? Shape{BM, BN, 2, 0.70, 0.90, 8.0}
-                     : which == kDirectWide ? Shape{32, 64, 2, 0.65, nt ? 0.72 : 0.85, 6.0}
+    const Shape sh = which == kTile         ? Shape{BM, BN, 2, 0.84, 0.94, 8.0}
+                     : which == kDirectWide ? Shape{32, 64, 2, 0.65, nt ? 0.66 : 0.80, 6.0}
                                             : Shape{32, 32, 4, 0.50, nt ? 0.58 : 0.68, 4.0};
     const double tiles = (double)((m + sh.bm - 1) / sh.bm) * ((n + sh.bn - 1) / sh.bn);
     const double one_us = 2.0 * sh.bm * sh.bn * (double)k / 0.307e6;
