@@ -10,9 +10,8 @@
 // Steps (all on the caller's stream):
 //  1. insert every value into an open-addressing hash set (linear probing,
 //     64-bit compare-and-swap);
-//  2. up to kSmallDict distinct values: one workgroup sorts them in LDS and
-//     writes each one's rank into a code array parallel to the table; every
-//     record's value is then looked up;
+//  2. up to kSmallDict distinct values: each one's rank among them goes into a
+//     code array parallel to the table, and every record's value is looked up;
 //  3. the host waits, for the count it returns;
 //  4. with more distinct values only then, and with grids of that count: the
 //     occupied slots compacted into a list, the list sorted (chunks of 2048 in
@@ -72,9 +71,8 @@ struct Table {
     unsigned long long mask, max_probes, max_count;
 };
 
-// Up to this many distinct values one workgroup sorts them (the insertion
-// lists their slots in LDS; a list of twice as many would cost it one of its
-// four workgroups per CU).
+// Up to this many distinct values the insertion lists their slots, in LDS first
+// (a list of twice as many would cost it one of its four workgroups per CU).
 constexpr int kSmallDict = 1024;
 
 // What the sort's kernels do first: the number of distinct values, or 0 when
@@ -115,7 +113,7 @@ __device__ inline void step_barrier(int kk, int j) {
 // 2^24 values with 32 distinct took 300 us against 46 us here (2.9 TB/s of
 // the column).  Columns with many distinct values mostly miss and go to the
 // table.
-constexpr int kInsThreads = 512, kSmallThreads = 512;
+constexpr int kInsThreads = 512;
 constexpr int kSeenBits = 12;       // LDS entries: 4096 (32 KB)
 constexpr unsigned kSeen = 1u << kSeenBits;
 
@@ -200,50 +198,34 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
         for (unsigned int i = threadIdx.x; i < got; i += kInsThreads) list[base + i] = mine[i];
 }
 
-// A small dictionary, by one workgroup: the listed slots' values sorted, slots
-// along with them, written to dict, and their ranks to the slots' codes.
-// (Done by the insertion's last workgroup to finish, this saved a launch and
-// cost 40 us at 2^24 values, for a count of finished workgroups and fences.)
-__global__ void __launch_bounds__(kSmallThreads)
+// A small dictionary, kRankValues values per workgroup: the listed slots' values
+// written to dict at their ranks, and the ranks to the slots' codes.  A value's
+// rank is counted, by kRankParts neighbouring lanes that each compare it with
+// an eighth of the values: 6 us for 512 of them, where one workgroup's bitonic
+// network took 11 (for runs of 2048 the network is the faster one).  (Done by
+// the insertion's last workgroup to finish, this saved a launch and cost 40 us
+// at 2^24 values, for a count of finished workgroups and fences.)
+constexpr int kRankThreads = 512, kRankParts = 8, kRankValues = kRankThreads / kRankParts;
+__global__ void __launch_bounds__(kRankThreads)
 dict_small_kernel(Table t, const unsigned int *__restrict__ list, const DictState *st,
                   long long *__restrict__ dict) {
     __shared__ long long val[kSmallDict];
-    __shared__ unsigned int slots[kSmallDict];
     const unsigned long long k = st->count;
+    const int first = (int)blockIdx.x * kRankValues;
     if (st->overflow || k > (unsigned long long)kSmallDict) return;
-    int P = 2;
-    while (P < (int)k) P *= 2;
-    for (int i = threadIdx.x; i < P; i += kSmallThreads) {
-        // padding: after every value, also one that equals it
-        const unsigned int slot = i < (int)k ? list[i] : 0xffffffffu;
-        val[i] = i < (int)k ? (long long)t.slot[slot] : 0x7fffffffffffffffll;
-        slots[i] = slot;
-    }
-    __syncthreads();
-    static_assert(kSmallDict <= 2 * kSmallThreads, "one pair per thread");
-    for (int kk = 2; kk <= P; kk *= 2)
-        for (int j = kk / 2; j > 0; j /= 2) {
-            const int p = threadIdx.x;
-            if (p < P / 2) {
-                const int i = ((p & ~(j - 1)) << 1) | (p & (j - 1)), l = i + j;
-                const long long x = val[i], y = val[l];
-                const unsigned int sx = slots[i], sy = slots[l];
-                if ((x > y || (x == y && sx > sy)) == ((i & kk) == 0)) {
-                    val[i] = y;
-                    val[l] = x;
-                    slots[i] = sy;
-                    slots[l] = sx;
-                }
-            }
-            step_barrier(kk, j);
-        }
-    __syncthreads();
     const int shift = st->has_min ? 1 : 0;
-    if (threadIdx.x == 0 && shift) dict[0] = (long long)kEmpty;
-    for (int i = threadIdx.x; i < (int)k; i += kSmallThreads) {
-        dict[i + shift] = val[i];
-        t.code[slots[i]] = i + shift;
-    }
+    if (first == 0 && threadIdx.x == 0 && shift) dict[0] = (long long)kEmpty;
+    if (first >= (int)k) return;
+    for (int i = threadIdx.x; i < (int)k; i += kRankThreads) val[i] = (long long)t.slot[list[i]];
+    __syncthreads();
+    const int i = first + (int)threadIdx.x / kRankParts, part = (int)threadIdx.x % kRankParts;
+    const long long v = val[min(i, (int)k - 1)];
+    int rank = 0;  // (the values differ)
+    for (int j = part; j < (int)k; j += kRankParts) rank += val[j] < v;
+    for (int d = 1; d < kRankParts; d <<= 1) rank += __shfl_xor(rank, d);
+    if (i >= (int)k || part != 0) return;
+    dict[rank + shift] = v;
+    t.code[list[i]] = rank + shift;
 }
 
 // The occupied slots as a list, in no particular order.  One atomic per
@@ -504,7 +486,7 @@ void enqueue_insert(const Columns &c, const Table &t, unsigned int *list, DictSt
     else
         dict_insert_kernel<8><<<stream_grid(c.n, kInsThreads * 8, 1024), kInsThreads, 0, s>>>(
             c.a, c.n_a, c.b, c.n, t, list, st);
-    dict_small_kernel<<<1, kSmallThreads, 0, s>>>(t, list, st, dict);
+    dict_small_kernel<<<kSmallDict / kRankValues, kRankThreads, 0, s>>>(t, list, st, dict);
 }
 
 void enqueue_lookup(const Columns &c, const Table &t, unsigned long long limit,
