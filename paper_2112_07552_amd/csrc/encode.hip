@@ -74,7 +74,10 @@ __device__ inline void report_skips(bool bad, StatusBlock *st, int which) {
 
 // UNIQUE: the caller promised unique (group, key) cells, so a plain store
 // replaces the atomic add (random 8-byte stores run about 3x faster than
-// device-scope FP64 atomics, which fetch the whole line first).
+// device-scope FP64 atomics, which fetch the whole line first).  The records
+// are read past the caches, which the matrix needs: 2^24 records into 134 MB 239
+// us, 225 so.  The random stores bound it (75 G records/s; 85 where one XCD
+// stores to 512 KB at a time, so neither memory nor the fabric does).
 template <typename T, bool UNIQUE>
 __global__ void __launch_bounds__(kThreads)
 encode_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ key,
@@ -83,11 +86,11 @@ encode_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restr
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     bool bad = false;
     if (i < n) {
-        const int g = grp[i], k = key[i];
+        const int g = __builtin_nontemporal_load(grp + i), k = __builtin_nontemporal_load(key + i);
         const int r = transpose ? k : g;
         const int c = transpose ? g : k;
         if ((unsigned)r < (unsigned)rows && (unsigned)c < (unsigned)cols) {
-            const double v = val ? (double)val[i] : 1.0;
+            const double v = val ? (double)__builtin_nontemporal_load(val + i) : 1.0;
             double *dst = out + (size_t)r * (size_t)cols + c;
             if (UNIQUE) *dst = v;
             else unsafeAtomicAdd(dst, v);
@@ -133,20 +136,22 @@ encode_pair_kernel(PairSide a, PairSide b, unsigned blocks_a, StatusBlock *st) {
     report_skips(bad, st, of_a ? 0 : 1);
 }
 
+// (Columns and results past the caches, as the encoding: 8.2 ms for 8.4 at 2^28
+// records, 429 us for 431 at 2^24.)
 __global__ void __launch_bounds__(kThreads)
 gather_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ key,
               int transpose, int rows, int cols, int r0, int r1, const double *__restrict__ src,
               double *__restrict__ dst) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= n) return;
-    const int g = grp[i], k = key[i];
+    const int g = __builtin_nontemporal_load(grp + i), k = __builtin_nontemporal_load(key + i);
     const int r = transpose ? k : g;
     const int c = transpose ? g : k;
     const bool valid = (unsigned)r < (unsigned)rows && (unsigned)c < (unsigned)cols;
     // a launch covers the records whose row lies in [r0, r1); the one that
     // starts at row 0 also writes the zeros of records outside the matrix
     if (valid ? (r < r0 || r >= r1) : r0 != 0) return;
-    dst[i] = valid ? src[(size_t)r * (size_t)cols + c] : 0.0;
+    __builtin_nontemporal_store(valid ? src[(size_t)r * (size_t)cols + c] : 0.0, dst + i);
 }
 
 // Both relations' gathers in one launch (workgroups as encode_pair_kernel):
