@@ -72,7 +72,7 @@ struct Table {
 };
 
 // Up to this many distinct values the insertion lists their slots, in LDS first
-// (a list of twice as many would cost it one of its four workgroups per CU).
+// (with a list of twice as many fewer of its workgroups would fit a CU).
 constexpr int kSmallDict = 1024;
 
 // What the sort's kernels do first: the number of distinct values, or 0 when
@@ -113,7 +113,7 @@ __device__ inline void step_barrier(int kk, int j) {
 // 2^24 values with 32 distinct took 300 us against 46 us here (2.9 TB/s of
 // the column).  Columns with many distinct values mostly miss and go to the
 // table.
-constexpr int kInsThreads = 512;
+constexpr int kInsThreads = 1024;
 constexpr int kSeenBits = 12;       // LDS entries: 4096 (32 KB)
 constexpr unsigned kSeen = 1u << kSeenBits;
 
@@ -123,19 +123,19 @@ constexpr unsigned kSeen = 1u << kSeenBits;
 // `mine` lists the slots this workgroup has filled, while they are few; each
 // workgroup adds its number to the count and, as long as all of them are at
 // most kSmallDict, its slots to `list`.
-template <int PER>
-__global__ void __launch_bounds__(kInsThreads)
+template <int PER, int THREADS>
+__global__ void __launch_bounds__(THREADS)
 dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long *__restrict__ b,
                    int64_t n, Table t, unsigned int *__restrict__ list, DictState *st) {
     __shared__ unsigned long long seen[kSeen];
     __shared__ unsigned int mine[kSmallDict];
     __shared__ unsigned int seen_min, full, filled;
     __shared__ unsigned long long base;
-    for (unsigned i = threadIdx.x; i < kSeen; i += kInsThreads) seen[i] = kEmpty;
+    for (unsigned i = threadIdx.x; i < kSeen; i += THREADS) seen[i] = kEmpty;
     if (threadIdx.x == 0) seen_min = full = filled = 0u;
     __syncthreads();
-    const int64_t step = (int64_t)gridDim.x * kInsThreads * PER;
-    for (int64_t i0 = (int64_t)blockIdx.x * kInsThreads * PER; i0 < n; i0 += step) {
+    const int64_t step = (int64_t)gridDim.x * THREADS * PER;
+    for (int64_t i0 = (int64_t)blockIdx.x * THREADS * PER; i0 < n; i0 += step) {
         // the table found full by anyone: leave (one lane asks for all)
         if (threadIdx.x == 0 &&
             __hip_atomic_load(&st->overflow, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
@@ -144,7 +144,7 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
         unsigned long long v[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const int64_t i = i0 + j * kInsThreads + threadIdx.x;
+            const int64_t i = i0 + j * THREADS + threadIdx.x;
             const int64_t c = i < n ? i : i0;  // past the end: a value again
             v[j] = (unsigned long long)(c < n_a ? a[c] : b[c - n_a]);
         }
@@ -195,7 +195,7 @@ dict_insert_kernel(const long long *__restrict__ a, int64_t n_a, const long long
     if (threadIdx.x == 0 && got > 0u) base = atomicAdd(&st->count, (unsigned long long)got);
     __syncthreads();
     if (got > 0u && base + got <= (unsigned long long)kSmallDict)
-        for (unsigned int i = threadIdx.x; i < got; i += kInsThreads) list[base + i] = mine[i];
+        for (unsigned int i = threadIdx.x; i < got; i += THREADS) list[base + i] = mine[i];
 }
 
 // A small dictionary, kRankValues values per workgroup: the listed slots' values
@@ -453,18 +453,20 @@ dict_lookup_kernel(const long long *__restrict__ a, int64_t n_a, const long long
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kThreads - 1) / kThreads); }
 
 // Workgroups of a kernel over the columns: `per` records each, at most `most`
-// of 512 threads (more records then take more rounds).
+// (more records then take more rounds).
 inline unsigned stream_grid(int64_t n, int per, int64_t most) {
     return (unsigned)std::min<int64_t>(most, (n + per - 1) / per);
 }
 
-// Columns by length: one value per thread while that takes one round of 512
-// workgroups; then 512 workgroups of four (fewer meet on the same few slots at
-// the start: 10^6 values with 500 distinct 106 us in all, 116 with 1024; 10^6 +
-// 10^6 with 10^5 172 and 171); from 2^21 values 1024 of eight (2^24 + 2^24
-// values with 32 distinct 211 us, 242 with four at a time, 259 with 512
-// workgroups of four).
-constexpr int64_t kShort = (int64_t)512 * kInsThreads, kMiddle = (int64_t)1 << 21;
+// Columns by length: one value per thread while that takes one round of 256
+// workgroups of 1024 threads (of 512 up to kTiny values: a value's probes are a
+// chain of memory round trips, so they go to more CUs); then those 256 with four
+// values per thread; from 2^21 values 512 workgroups with eight.  Fewer and larger
+// workgroups meet less often on the same few slots at the start: us per call with
+// 512 threads and twice the workgroups, and now: 2^24 + 2^24 values, 32 distinct
+// 182 and 167; 2^24 110 and 97; 10^6, 500 distinct 78 and 72; 10^5 + 10^5, 200
+// distinct 63 and 55; (eight values at a time against four: 211 and 242).
+constexpr int64_t kTiny = 65536, kShort = (int64_t)256 * kInsThreads, kMiddle = (int64_t)1 << 21;
 
 struct Columns {
     const long long *a, *b;
@@ -477,15 +479,18 @@ void enqueue_insert(const Columns &c, const Table &t, unsigned int *list, DictSt
     const size_t clear_blocks = ((size_t)t.mask + kThreads) / kThreads;
     dict_clear_kernel<<<(unsigned)std::min<size_t>(clear_blocks, 65536), kThreads, 0, s>>>(t, st);
     if (c.n == 0) return;
-    if (c.n <= kShort)
-        dict_insert_kernel<1><<<stream_grid(c.n, kInsThreads, 512), kInsThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, t, list, st);
+    if (c.n <= kTiny)
+        dict_insert_kernel<1, 512><<<stream_grid(c.n, 512, 128), 512, 0, s>>>(c.a, c.n_a, c.b, c.n,
+                                                                              t, list, st);
+    else if (c.n <= kShort)
+        dict_insert_kernel<1, kInsThreads><<<stream_grid(c.n, kInsThreads, 256), kInsThreads, 0,
+                                             s>>>(c.a, c.n_a, c.b, c.n, t, list, st);
     else if (c.n <= kMiddle)
-        dict_insert_kernel<4><<<stream_grid(c.n, kInsThreads * 4, 512), kInsThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, t, list, st);
+        dict_insert_kernel<4, kInsThreads><<<stream_grid(c.n, kInsThreads * 4, 256), kInsThreads,
+                                             0, s>>>(c.a, c.n_a, c.b, c.n, t, list, st);
     else
-        dict_insert_kernel<8><<<stream_grid(c.n, kInsThreads * 8, 1024), kInsThreads, 0, s>>>(
-            c.a, c.n_a, c.b, c.n, t, list, st);
+        dict_insert_kernel<8, kInsThreads><<<stream_grid(c.n, kInsThreads * 8, 512), kInsThreads,
+                                             0, s>>>(c.a, c.n_a, c.b, c.n, t, list, st);
     dict_small_kernel<<<kSmallDict / kRankValues, kRankThreads, 0, s>>>(t, list, st, dict);
 }
 
