@@ -419,8 +419,12 @@ dict_lookup_kernel(const long long *__restrict__ a, int64_t n_a, const long long
         }
         __syncthreads();
     }
-    const int64_t step = (int64_t)gridDim.x * kLookThreads * PER;
-    for (int64_t i0 = (int64_t)blockIdx.x * kLookThreads * PER; i0 < n; i0 += step) {
+    // from the columns' end: what the insertion read last is still in the
+    // last-level cache
+    constexpr int64_t kPart = (int64_t)kLookThreads * PER;
+    const int64_t parts = (n + kPart - 1) / kPart;
+    for (int64_t q = blockIdx.x; q < parts; q += gridDim.x) {
+        const int64_t i0 = (parts - 1 - q) * kPart;
         unsigned long long v[PER];
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
