@@ -403,8 +403,8 @@ tcu_status tcu_mfma_peak(int kind, int32_t iters, void *out, hipStream_t stream)
  * signed 64-bit).  codes_a[i] = the rank of a[i] in that list (0-based), and
  * likewise codes_b; dict (capacity n_a + n_b) receives v_1..v_k and *k (a
  * host pointer) receives k.  Codes are independent of record order.  The
- * call SYNCHRONISES the stream once (to size the sort of the distinct
- * values).  n_a + n_b must not exceed 2^31 - 1.  ws: at least
+ * call SYNCHRONISES the stream once (for *k; the sort of more than 1024
+ * distinct values and their codes are enqueued after that).  n_a + n_b must not exceed 2^31 - 1.  ws: at least
  * tcu_dict_workspace_bytes(n_a + n_b) bytes, 256-byte aligned (about 24
  * bytes per value); errors are returned, not recorded in ws. */
 size_t tcu_dict_workspace_bytes(int64_t n);

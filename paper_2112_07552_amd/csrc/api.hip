@@ -954,7 +954,7 @@ tcu_status tcu_join_agg_bwd(const tcu_relation *A, const tcu_relation *B, int32_
         // when that costs no extra round of workgroups: the dB gather of the
         // first block's records runs on the side stream beside the second
         // block's product, and only the second block's gather stays behind.
-        const int k1 = (both && !mixed) ? gemm_f64_row_cut(K, N) : 0;
+        const int k1 = (both && !mixed) ? gemm_f64_row_cut(K, N, M) : 0;
         if (k1 > 0) {
             TCU_TRY(launch_gemm_f64(1, 0, k1, N, M, X, K, dC, N, G2, N, stream));
             TCU_TRY(hipEventRecord(ev_fork, stream));

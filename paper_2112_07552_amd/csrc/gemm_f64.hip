@@ -678,7 +678,7 @@ hipError_t launch_gemm_f64_split(int trans_a, int trans_b, int m, int n, int k, 
     return launch_split<false, true>(m, n, k, A, lda, B, ldb, C, ldc, part, parts, s);
 }
 
-int gemm_f64_row_cut(int m, int n) {
+int gemm_f64_row_cut(int m, int n, int k) {
     const int cus = device_cus();
     if (cus <= 0) return 0;
     // two workgroups per CU: each is 4 waves, and the kernel runs 2 waves per SIMD
@@ -694,7 +694,10 @@ int gemm_f64_row_cut(int m, int n) {
         if (rounds(r * ct) + rounds((rt - r) * ct) != whole) continue;
         if (best == 0 || skew(r) < skew(best)) best = r;
     }
-    return (int)(best * BM);
+    // the whole and both parts on one kernel, so that the cut changes no bit
+    const int m1 = (int)(best * BM);
+    auto tile = [&](int rows) { return pick_kernel(false, false, rows, n, k, m, n) == kTile; };
+    return m1 > 0 && tile(m) && tile(m1) && tile(m - m1) ? m1 : 0;
 }
 
 hipError_t launch_gemm_f64(int trans_a, int trans_b, int m, int n, int k, const double *A,

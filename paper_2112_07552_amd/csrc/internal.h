@@ -178,10 +178,10 @@ hipError_t launch_gemm_f64_split(int trans_a, int trans_b, int m, int n, int k, 
                                  int64_t lda, const double *B, int64_t ldb, double *C,
                                  int64_t ldc, double *part, hipStream_t s);
 // Rows m1 (a multiple of the tile height, 0 < m1 < m) at which an m x n FP64
-// product can be cut into two launches that together take no more rounds of
+// product A^T B (contraction k, dense operands) can be cut into two launches that together take no more rounds of
 // concurrently resident workgroups than one launch; 0 when no such cut exists
 // or the product fills at most one round.
-int gemm_f64_row_cut(int m, int n);
+int gemm_f64_row_cut(int m, int n, int k);
 
 // count.hip: the product of two 0/1 encodings (relations with unique cells,
 // values ignored) on int8 planes, as doubles into C and / or int32 into cnt
