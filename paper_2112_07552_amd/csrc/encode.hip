@@ -72,13 +72,22 @@ __device__ inline void report_skips(bool bad, StatusBlock *st, int which) {
     }
 }
 
+// One element of a column, past the caches or through them.
+template <bool PAST, typename T>
+__device__ inline T column(const T *p, int64_t i) {
+    return PAST ? __builtin_nontemporal_load(p + i) : p[i];
+}
+
 // UNIQUE: the caller promised unique (group, key) cells, so a plain store
 // replaces the atomic add (random 8-byte stores run about 3x faster than
-// device-scope FP64 atomics, which fetch the whole line first).  The records
-// are read past the caches, which the matrix needs: 2^24 records into 134 MB 239
-// us, 225 so.  The random stores bound it (75 G records/s; 85 where one XCD
-// stores to 512 KB at a time, so neither memory nor the fabric does).
-template <typename T, bool UNIQUE>
+// device-scope FP64 atomics, which fetch the whole line first).  PAST: the
+// records are read past the caches, which the matrix needs (past_caches): 2^24
+// records into 134 MB 239 us, 225 so.  Smaller columns may still be cached from
+// the kernel that wrote them, and the pair kernel reads them through the caches:
+// 2^20 records 85 us for the whole forward, 92 past them.  The random stores bound it (75 G
+// records/s; 85 where one XCD stores to 512 KB at a time, so neither memory nor
+// the fabric does).
+template <typename T, bool UNIQUE, bool PAST>
 __global__ void __launch_bounds__(kThreads)
 encode_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ key,
               const T *__restrict__ val, int transpose, int rows, int cols,
@@ -86,11 +95,11 @@ encode_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restr
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     bool bad = false;
     if (i < n) {
-        const int g = __builtin_nontemporal_load(grp + i), k = __builtin_nontemporal_load(key + i);
+        const int g = column<PAST>(grp, i), k = column<PAST>(key, i);
         const int r = transpose ? k : g;
         const int c = transpose ? g : k;
         if ((unsigned)r < (unsigned)rows && (unsigned)c < (unsigned)cols) {
-            const double v = val ? (double)__builtin_nontemporal_load(val + i) : 1.0;
+            const double v = val ? (double)column<PAST>(val, i) : 1.0;
             double *dst = out + (size_t)r * (size_t)cols + c;
             if (UNIQUE) *dst = v;
             else unsafeAtomicAdd(dst, v);
@@ -136,22 +145,25 @@ encode_pair_kernel(PairSide a, PairSide b, unsigned blocks_a, StatusBlock *st) {
     report_skips(bad, st, of_a ? 0 : 1);
 }
 
-// (Columns and results past the caches, as the encoding: 8.2 ms for 8.4 at 2^28
-// records, 429 us for 431 at 2^24.)
+// (PAST: columns and results past the caches, as the encoding: 8.2 ms for 8.4 at
+// 2^28 records.)
+template <bool PAST>
 __global__ void __launch_bounds__(kThreads)
 gather_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ key,
               int transpose, int rows, int cols, int r0, int r1, const double *__restrict__ src,
               double *__restrict__ dst) {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= n) return;
-    const int g = __builtin_nontemporal_load(grp + i), k = __builtin_nontemporal_load(key + i);
+    const int g = column<PAST>(grp, i), k = column<PAST>(key, i);
     const int r = transpose ? k : g;
     const int c = transpose ? g : k;
     const bool valid = (unsigned)r < (unsigned)rows && (unsigned)c < (unsigned)cols;
     // a launch covers the records whose row lies in [r0, r1); the one that
     // starts at row 0 also writes the zeros of records outside the matrix
     if (valid ? (r < r0 || r >= r1) : r0 != 0) return;
-    __builtin_nontemporal_store(valid ? src[(size_t)r * (size_t)cols + c] : 0.0, dst + i);
+    const double v = valid ? src[(size_t)r * (size_t)cols + c] : 0.0;
+    if (PAST) __builtin_nontemporal_store(v, dst + i);
+    else dst[i] = v;
 }
 
 // Both relations' gathers in one launch (workgroups as encode_pair_kernel):
@@ -440,6 +452,29 @@ hipError_t launch_set_plan(StatusBlock *st, uint32_t slices, uint32_t bits, uint
     return hipGetLastError();
 }
 
+namespace {
+
+// Whether a kernel over columns of `bytes` and a matrix of `cells` doubles takes
+// the columns past the caches: from about a quarter of the last-level one, since
+// the operator's other matrices want the rest.  Whole FP64 steps, us, always
+// past and through them: 1500^3 (54 MB) 625 and 589, 2048^3 (101 MB) 1071 and
+// 1088, 3000^3 3355 and 3397.
+bool past_caches(size_t bytes, size_t cells) {
+    return bytes + cells * sizeof(double) > ((size_t)72 << 20);
+}
+
+template <typename T>
+void encode_launch(const tcu_relation &R, const T *val, bool unique, bool past, unsigned grid,
+                   int transpose, int rows, int cols, double *out, StatusBlock *st, int which,
+                   hipStream_t s) {
+    auto *kernel = unique ? (past ? encode_kernel<T, true, true> : encode_kernel<T, true, false>)
+                          : (past ? encode_kernel<T, false, true> : encode_kernel<T, false, false>);
+    kernel<<<grid, kThreads, 0, s>>>(R.n, R.group, R.key, val, transpose, rows, cols, out, st,
+                                     which);
+}
+
+}  // namespace
+
 hipError_t launch_encode(const tcu_relation &R, int transpose, int rows, int cols, double *out,
                          StatusBlock *st, int which, hipStream_t s) {
     if (R.n == 0) return hipSuccess;
@@ -450,25 +485,12 @@ hipError_t launch_encode(const tcu_relation &R, int transpose, int rows, int col
     const bool unique = (R.flags & TCU_REL_UNIQUE_CELLS) != 0;
     const float *vf = static_cast<const float *>(R.val);
     const double *vd = static_cast<const double *>(R.val);
-    if (R.dtype == TCU_F32) {
-        if (unique)
-            encode_kernel<float, true><<<grid, kThreads, 0, s>>>(R.n, R.group, R.key, vf,
-                                                                 transpose, rows, cols, out, st,
-                                                                 which);
-        else
-            encode_kernel<float, false><<<grid, kThreads, 0, s>>>(R.n, R.group, R.key, vf,
-                                                                  transpose, rows, cols, out, st,
-                                                                  which);
-    } else {
-        if (unique)
-            encode_kernel<double, true><<<grid, kThreads, 0, s>>>(R.n, R.group, R.key, vd,
-                                                                  transpose, rows, cols, out, st,
-                                                                  which);
-        else
-            encode_kernel<double, false><<<grid, kThreads, 0, s>>>(R.n, R.group, R.key, vd,
-                                                                   transpose, rows, cols, out,
-                                                                   st, which);
-    }
+    const bool past =
+        past_caches((size_t)R.n * (size_t)(8 + (int)vbytes), (size_t)rows * (size_t)cols);
+    if (R.dtype == TCU_F32)
+        encode_launch(R, vf, unique, past, grid, transpose, rows, cols, out, st, which, s);
+    else
+        encode_launch(R, vd, unique, past, grid, transpose, rows, cols, out, st, which, s);
     return hipGetLastError();
 }
 
@@ -639,8 +661,11 @@ hipError_t launch_gather(const tcu_relation &R, int transpose, int rows, int col
     if (r1 < 0) r1 = rows;
     // algorithmic bytes: group and key in, one 8-byte cell in, 8 bytes out
     TraceScope ts(TCU_KERNEL_GATHER, rows, cols, 0, 1, (double)R.n * 24.0, s);
-    gather_kernel<<<grid_for(R.n), kThreads, 0, s>>>(R.n, R.group, R.key, transpose, rows, cols,
-                                                     r0, r1, src, dst);
+    auto *kernel = past_caches((size_t)R.n * 16, (size_t)rows * (size_t)cols)
+                       ? gather_kernel<true>
+                       : gather_kernel<false>;
+    kernel<<<grid_for(R.n), kThreads, 0, s>>>(R.n, R.group, R.key, transpose, rows, cols, r0, r1,
+                                              src, dst);
     return hipGetLastError();
 }
 
