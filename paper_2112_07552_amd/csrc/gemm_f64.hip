@@ -202,14 +202,24 @@ __device__ inline void tile_coords(int m, int n, int &tm, int &tn) {
 // B_KC: op(B)'s contraction index is contiguous (trans_b == 1).
 // Every tile is whole: edge tiles are moved back to end at m (or n), and the
 // stores skip the cells a moved tile shares with its neighbour.
+// kc > 0: split contraction, workgroup row y of the grid multiplies the chunk
+// [y kc, (y + 1) kc) of k (at least BK of it) into its own partial product at C +
+// y cstride.
 template <bool A_KC, bool B_KC>
 __global__ void __launch_bounds__(THREADS) __attribute__((amdgpu_waves_per_eu(2, 2)))
 gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
                 const double *__restrict__ B, int64_t ldb, double *__restrict__ C, int64_t ldc,
-                int accumulate, const uint32_t *only_if) {
+                int accumulate, int kc, int64_t cstride, const uint32_t *only_if) {
     if (only_if != nullptr && *only_if == 0u) return;
     __shared__ __attribute__((aligned(16))) double lds_a[2][Tile<A_KC>::elems];
     __shared__ __attribute__((aligned(16))) double lds_b[2][Tile<B_KC>::elems];
+    if (kc > 0) {
+        const int c0 = (int)blockIdx.y * kc;
+        A += A_KC ? (int64_t)c0 : (int64_t)c0 * lda;
+        B += B_KC ? (int64_t)c0 : (int64_t)c0 * ldb;
+        C += (int64_t)blockIdx.y * cstride;
+        k = min(kc, k - c0);
+    }
 
     int tm, tn;
     tile_coords<BM, BN>(m, n, tm, tn);
@@ -293,8 +303,6 @@ gemm_f64_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
     }
 }
 
-constexpr int kRunStages = 256 / BK;
-
 // ----- direct path: small tiles, fragments straight from memory.  A
 // workgroup's four waves share one tile of 16 TM x 16 TN cells and split the
 // contraction, so a wave needs neither LDS nor barriers until the four partial
@@ -375,19 +383,21 @@ __device__ __forceinline__ void fold_run(d4 (&acc)[TM][TN], double *run, bool fi
             }
 }
 
-// The stages 0 .. S - 1 of 16 k, S >= 1.  An accumulator takes at most kRunStages
-// of them (256 terms of k) before its run is folded away: the error of a sum
-// grows with the length of its chain of additions, and the split contraction of
-// 128 x 128 tiles that these kernels stand in for adds chunks of 256 terms and
-// more.  Relative RMS error of uniform values with that split, with one chain
-// per wave, and with runs: 1024 x 1024 x 8192 2.9e-16, 5.9e-16 and 1.0e-16; 300 x
-// 500 x 20000 2.1e-16, 1.05e-15 and 1.1e-16.  The runs cost no time (1024 x 1024
-// x 8192 289 and 291 us).
+// The stages 0 .. S - 1 of 16 k, S >= 1, of `total` (one more where a remainder
+// of k follows them).  An accumulator takes at most `stages`
+// of them before its run is folded away: the error of a sum grows with the length
+// of its chain of additions, and where these kernels stand in for the split
+// contraction of 128 x 128 tiles, runs are no longer than its chunks. Relative
+// RMS error of uniform values with that split, with one chain per wave, and with
+// runs: 1024 x 1024 x 4096 2.3e-16, 4.1e-16 and 2.0e-16; 1408 x 1408 x 8192
+// 5.0e-16, 5.8e-16 and 3.0e-16.  A fold takes about 1% of a run of 256 terms on
+// the 32 x 32 tiles and 2% on the 32 x 64 ones (1024 x 1024 x 2048, two folds: 67.4
+// and 70.7 us).
 // Returns whether a run has been folded.
 template <bool A_KC, bool B_KC, int TM, int TN, bool EDGE, bool WIDE>
 __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa,
                                               const DirectOp<B_KC, TN, WIDE> &ob, int S,
-                                              d4 (&acc)[TM][TN], double *run) {
+                                              int total, int stages, d4 (&acc)[TM][TN], double *run) {
     constexpr int NB = TM * TN > 4 ? 3 : 2;  // stages in registers
     constexpr int IA = direct_items<A_KC, TM, EDGE>(), IB = direct_items<B_KC, TN, EDGE>();
     constexpr int MF = 4 * TM * TN;
@@ -403,8 +413,10 @@ __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa
 #pragma unroll
         for (int i = 0; i < IB; ++i) direct_load<B_KC, TN, EDGE, WIDE>(ob, bb, i, fb[u]);
     }
-    constexpr int kFold = kRunStages / NB * NB;
-    int next = kFold;
+    // runs of equal length, in whole rounds of NB stages
+    const int runs = (total + stages - 1) / stages;
+    const int fold = min((total + runs * NB - 1) / (runs * NB), stages / NB) * NB;
+    int next = fold;
     for (int s = 0; s < S; s += NB) {
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -430,12 +442,12 @@ __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (s + NB == next && S - next > kRunStages - kFold) {
-            fold_run<TM, TN>(acc, run, next == kFold);
-            next += kFold;
+        if (s + NB == next && total - next > stages - fold) {
+            fold_run<TM, TN>(acc, run, next == fold);
+            next += fold;
         }
     }
-    return next > kFold;
+    return next > fold;
 }
 
 // The last `left` (1 .. 15) values of k, past them zeros on both sides.
@@ -456,13 +468,12 @@ __device__ __forceinline__ void direct_tail(const DirectOp<KC, F, WIDE> &o, int 
         }
 }
 
-// kc > 0: split contraction, workgroup row y of the grid multiplies the chunk
-// [y kc, (y + 1) kc) of k into its own partial product at C + y cstride.
+// kc > 0: split contraction, as gemm_f64_kernel.  stages: of a run (direct_stages), at least 16.
 template <bool A_KC, bool B_KC, int TM, int TN, bool WIDE>
 __global__ void __launch_bounds__(THREADS)
 gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
                    const double *__restrict__ B, int64_t ldb, double *__restrict__ C,
-                   int64_t ldc, int accumulate, int kc, int64_t cstride,
+                   int64_t ldc, int accumulate, int kc, int64_t cstride, int stages,
                    const uint32_t *only_if) {
     if (only_if != nullptr && *only_if == 0u) return;
     constexpr int TILE_M = 16 * TM, TILE_N = 16 * TN, W = THREADS / 64, E = 4 * TM * TN;
@@ -492,13 +503,14 @@ gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t ld
 #pragma unroll
         for (int b = 0; b < TN; ++b) acc[a][b] = d4{0.0, 0.0, 0.0, 0.0};
     const int S = (k1 - k0) / BK, left = (k1 - k0) % BK;
+    const int total = S + (left > 0 ? 1 : 0);
     double *run = red + wave * E * 64 + lane;
     bool folded = false;
     if (S > 0) {
         if ((A_KC || m0 + TILE_M <= m) && (B_KC || n0 + TILE_N <= n))
-            folded = direct_stages<A_KC, B_KC, TM, TN, false, WIDE>(oa, ob, S, acc, run);
+            folded = direct_stages<A_KC, B_KC, TM, TN, false, WIDE>(oa, ob, S, total, stages, acc, run);
         else
-            folded = direct_stages<A_KC, B_KC, TM, TN, true, WIDE>(oa, ob, S, acc, run);
+            folded = direct_stages<A_KC, B_KC, TM, TN, true, WIDE>(oa, ob, S, total, stages, acc, run);
     }
     if (left > 0) {
         double fa[TM][4], fb[TN][4];
@@ -534,6 +546,8 @@ gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t ld
 
 // ------------------------------------------------------------- host side
 
+constexpr int kOneRun = 0x7fffffff / 64;  // stages: no run is folded
+
 // The kernels a product can run on.
 enum Kernel { kTile, kDirectWide, kDirectSmall };  // 128 x 128; 32 x 64; 32 x 32
 
@@ -545,19 +559,25 @@ enum Kernel { kTile, kDirectWide, kDirectSmall };  // 128 x 128; 32 x 64; 32 x 3
 // 8.4; 1024^3 126, 43, 45; 2048^3 278, 306, 332; 4096^3 1867, 1998, -; 1500 x
 // 2777 x 2051 (264 tiles) 478, 336, 342; 3000^3 1030, 846, -.  The direct kernels
 // read both operands of A B^T in 64-byte pieces of many rows, which costs them
-// more (2048^3: 368, the tile kernel 265).
-double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus) {
+// more (2048^3: 368, the tile kernel 265; 1024 x 1024 x 8192 365 and 266 TN, 512 x
+// 512 x 16384 226 and 143).
+// parts: that many such products, of k each, in one launch.
+double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus, int parts = 1) {
     struct Shape {
         int bm, bn, per_cu;
         double one, full, fixed;
     };
-    const Shape sh = which == kTile         ? Shape{BM, BN, 2, 0.84, 0.94, 8.0}
-                     : which == kDirectWide ? Shape{32, 64, 2, 0.65, nt ? 0.66 : 0.80, 6.0}
-                                            : Shape{32, 32, 4, 0.50, nt ? 0.58 : 0.68, 4.0};
-    const double tiles = (double)((m + sh.bm - 1) / sh.bm) * ((n + sh.bn - 1) / sh.bn);
+    const Shape sh =
+        which == kTile         ? Shape{BM, BN, 2, 0.84, 0.94, 8.0}
+        : which == kDirectWide ? Shape{32, 64, 2, nt ? 0.62 : 0.65, nt ? 0.62 : 0.80, 6.0}
+                               : Shape{32, 32, 4, 0.50, nt ? 0.50 : 0.68, 4.0};
+    const double tiles =
+        (double)((m + sh.bm - 1) / sh.bm) * ((n + sh.bn - 1) / sh.bn) * parts;
     const double one_us = 2.0 * sh.bm * sh.bn * (double)k / 0.307e6;
     const double rounds = floor(tiles / (sh.per_cu * cus));
-    const double w = ceil((tiles - rounds * sh.per_cu * cus) / cus);
+    const double left = tiles - rounds * sh.per_cu * cus;
+    // (chunks of 128 x 128 tiles do not spread one to a CU beyond a few)
+    const double w = which == kTile && parts > 1 && left > cus / 4 ? 2.0 : ceil(left / cus);
     double us = sh.fixed + rounds * sh.per_cu * one_us / sh.full;
     if (w > 0) us += w * one_us / (sh.one + (sh.full - sh.one) * (w - 1) / (sh.per_cu - 1));
     return us;
@@ -591,16 +611,41 @@ Kernel pick_kernel(bool a_kc, bool b_kc, int m, int n, int k, int64_t lda, int64
 template <bool A_KC, bool B_KC, int TM, int TN>
 void launch_direct(int m, int n, int k, const double *A, int64_t lda, const double *B,
                    int64_t ldb, double *C, int64_t ldc, int accumulate, int kc, int parts,
-                   const uint32_t *only_if, hipStream_t s) {
+                   int stages, const uint32_t *only_if, hipStream_t s) {
     const int64_t cstride = (int64_t)m * n;
     const dim3 grid((unsigned)(((m + 16 * TM - 1) / (16 * TM)) * ((n + 16 * TN - 1) / (16 * TN))),
                     (unsigned)parts);
     if (offsets_fit(A_KC, std::min(m, 16 * TM), lda) && offsets_fit(B_KC, std::min(n, 16 * TN), ldb))
         gemm_direct_kernel<A_KC, B_KC, TM, TN, false><<<grid, THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, only_if);
+            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, stages, only_if);
     else
         gemm_direct_kernel<A_KC, B_KC, TM, TN, true><<<grid, THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, only_if);
+            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, stages, only_if);
+}
+
+// The product on kernel `which`; parts > 1: in chunks of kc of k, their partial
+// products one after the other at C (ldc = n).  stages: of the direct kernels' runs.
+template <bool A_KC, bool B_KC>
+void launch_on(Kernel which, int m, int n, int k, const double *A, int64_t lda, const double *B,
+               int64_t ldb, double *C, int64_t ldc, int accumulate, int kc, int parts,
+               int stages, const uint32_t *only_if, hipStream_t s) {
+    switch (which) {
+        case kTile: {
+            const dim3 grid((unsigned)(((m + BM - 1) / BM) * ((n + BN - 1) / BN)),
+                            (unsigned)parts);
+            gemm_f64_kernel<A_KC, B_KC><<<grid, THREADS, 0, s>>>(
+                m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, (int64_t)m * n, only_if);
+            break;
+        }
+        case kDirectWide:
+            launch_direct<A_KC, B_KC, 2, 4>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, parts,
+                                            stages, only_if, s);
+            break;
+        case kDirectSmall:
+            launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, parts,
+                                            stages, only_if, s);
+            break;
+    }
 }
 
 template <bool A_KC, bool B_KC>
@@ -608,22 +653,8 @@ hipError_t launch(int m, int n, int k, const double *A, int64_t lda, const doubl
                   int64_t ldb, double *C, int64_t ldc, int accumulate, const uint32_t *only_if,
                   hipStream_t s) {
     TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, 1, 2.0 * m * n * (double)k, s);
-    switch (pick_kernel(A_KC, B_KC, m, n, k, lda, ldb)) {
-        case kTile: {
-            const int tiles = ((m + BM - 1) / BM) * ((n + BN - 1) / BN);
-            gemm_f64_kernel<A_KC, B_KC><<<tiles, THREADS, 0, s>>>(m, n, k, A, lda, B, ldb, C, ldc,
-                                                                 accumulate, only_if);
-            break;
-        }
-        case kDirectWide:
-            launch_direct<A_KC, B_KC, 2, 4>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1,
-                                            only_if, s);
-            break;
-        case kDirectSmall:
-            launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, C, ldc, accumulate, 0, 1,
-                                            only_if, s);
-            break;
-    }
+    launch_on<A_KC, B_KC>(pick_kernel(A_KC, B_KC, m, n, k, lda, ldb), m, n, k, A, lda, B, ldb, C,
+                          ldc, accumulate, 0, 1, kOneRun, only_if, s);
     return hipGetLastError();
 }
 
@@ -640,9 +671,9 @@ sum_partials_kernel(int m, int n, int parts, const double *__restrict__ part,
     C[(i / n) * ldc + i % n] = s;
 }
 
-// Partial products the workspace of tcu_gemm_f64_workspace_bytes has room for
-// (its size is the ABI's): outputs of fewer than 128 tiles of 128 x 128, k at
-// least 1024.  0: none.
+// Partial products the workspace has room for, one per chunk of k: outputs of
+// fewer than 128 tiles of 128 x 128, k at least 1024; two workgroups per CU,
+// chunks of at least 256.  0: none.
 int split_room(int m, int n, int k) {
     const int64_t tiles = (int64_t)((m + BM - 1) / BM) * ((n + BN - 1) / BN);
     if (tiles >= 128 || k < 1024) return 0;
@@ -651,34 +682,86 @@ int split_room(int m, int n, int k) {
     return parts >= 2 ? (int)parts : 0;
 }
 
-// Chunks of the split contraction, for outputs of so few 32 x 32 tiles that
-// they leave most CUs idle: one workgroup per CU, each chunk at least 256 deep
-// (four stages per wave; below that the sum's launch costs more than it
-// saves).  64 x 64 x 4096: 38 us in one piece, 9.9 us in 16.  Larger outputs
-// are not split: 1024^3 takes 54 us and 8 for the sum in four chunks of 128 x
-// 128 tiles, 38 us in one piece of 32 x 64 ones.  0: no split.
-int split_parts(int m, int n, int k) {
-    const int64_t tiles = (int64_t)((m + 31) / 32) * ((n + 31) / 32);
-    const int room = split_room(m, n, k);
-    if (tiles > 128 || room == 0) return 0;
-    const int64_t parts = std::min<int64_t>((256 + tiles - 1) / tiles, room);
-    return parts >= 2 ? (int)parts : 0;
-}
-
 int split_chunk(int k, int parts) { return ((k + parts - 1) / parts + BK - 1) / BK * BK; }
+
+// How a product with room for partial products runs: on the direct kernels in
+// one piece or in as many chunks as give each CU one, two or four workgroups, or
+// on the tile kernel in as many as there is room for (fewer would lengthen its
+// chains of additions; the direct kernels' do not follow the chunks).  Few 32 x 32
+// tiles take one workgroup per CU (64 x 64 x 4096 in 16 chunks 10.5 us, in one
+// piece 40); elsewhere the estimate above decides, with a margin for its errors,
+// which for chunks on the direct kernels reach a quarter.  us in one piece, on the
+// tile kernel, on the direct kernels split, * taken: 1024^3 43* 52 -; 1024 x 1024 x
+// 8192 NT 365 267* -; 512 x 512 x 65536 810 490* 540; 1024 x 128 x 65536 834 294*
+// 442; 300 x 500 x 20000 267 134* 147; 100 x 1500 x 30000 411 - 218*; 768 x 768 x
+// 8192 218 193* 190; 1408 x 1408 x 8192 510* 748 -.
+struct SplitPlan {
+    Kernel which;
+    int parts;
+};
+
+SplitPlan pick_split(bool a_kc, bool b_kc, int m, int n, int k, int64_t lda, int64_t ldb) {
+    const int room = split_room(m, n, k);
+    const int tiles = ((m + 31) / 32) * ((n + 31) / 32);
+    // few tiles: one workgroup per CU
+    const int few = tiles <= 128 ? std::min((256 + tiles - 1) / tiles, room) : 1;
+    const int kt = split_chunk(k, room);
+    const bool tile_ok = m >= BM && n >= BN && (k % kt == 0 || k % kt >= BK) &&
+                         offsets_fit(a_kc, BM, lda) && offsets_fit(b_kc, BN, ldb);
+    SplitPlan best{kDirectSmall, few};
+    if (tiles <= 128 && !tile_ok) return best;
+    const int cus = std::max(1, device_cus());
+    const bool nt = a_kc && b_kc;
+    auto estimate = [&](Kernel which, int parts) {
+        const int kc = parts > 1 ? split_chunk(k, parts) : k;
+        const int used = (k + kc - 1) / kc;
+        double us = kernel_us(which, nt, m, n, kc, cus, used);
+        // the sum of the partial products: a launch, and one cell's loads one
+        // after the other or all cells' bytes
+        if (used > 1) us += 4.0 + std::max(0.22 * used, (used + 1) * (8.0 * m * n / 4.0e6));
+        return us;
+    };
+    double best_us = estimate(kDirectSmall, few);
+    // taken where the estimate is `margin` of the others' or less
+    auto consider = [&](Kernel which, int parts, double margin) {
+        parts = std::min(parts, room);
+        if (parts < 2 && margin < 1.0) return;
+        const double us = estimate(which, parts) / margin;
+        if (us >= best_us) return;
+        best_us = us;
+        best = SplitPlan{which, parts};
+    };
+    if (tiles > 128) {
+        const int wide = ((m + 31) / 32) * ((n + 63) / 64);
+        consider(kDirectWide, 1, 1.0);
+        consider(kDirectWide, 2 * cus / wide, 0.75);
+        for (int w = 1; w <= 4; w *= 2) {
+            consider(kDirectSmall, w * cus / tiles, 0.75);
+            consider(kDirectSmall, (w * cus + tiles - 1) / tiles, 0.75);
+        }
+    }
+    if (tile_ok) consider(kTile, room, 0.93);
+    return best;
+}
 
 template <bool A_KC, bool B_KC>
 hipError_t launch_split(int m, int n, int k, const double *A, int64_t lda, const double *B,
-                        int64_t ldb, double *C, int64_t ldc, double *part, int parts,
-                        hipStream_t s) {
-    const int kc = split_chunk(k, parts);
-    const int used = (k + kc - 1) / kc;  // chunks that hold part of k
+                        int64_t ldb, double *C, int64_t ldc, double *part, hipStream_t s) {
+    const SplitPlan p = pick_split(A_KC, B_KC, m, n, k, lda, ldb);
+    const int kc = p.parts > 1 ? split_chunk(k, p.parts) : 0;
+    const int used = kc > 0 ? (k + kc - 1) / kc : 1;  // chunks that hold part of k
     {
         TraceScope ts(TCU_KERNEL_GEMM_F64, m, n, k, used, 2.0 * m * n * (double)k, s);
-        launch_direct<A_KC, B_KC, 2, 2>(m, n, k, A, lda, B, ldb, part, n, 0, kc, used, nullptr, s);
+        const int stages = split_chunk(k, split_room(m, n, k)) / BK;
+        if (used == 1)
+            launch_on<A_KC, B_KC>(p.which, m, n, k, A, lda, B, ldb, C, ldc, 0, 0, 1, stages,
+                                  nullptr, s);
+        else
+            launch_on<A_KC, B_KC>(p.which, m, n, k, A, lda, B, ldb, part, n, 0, kc, used, stages,
+                                  nullptr, s);
     }
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || used == 1) return e;
     const int64_t mn = (int64_t)m * n;
     sum_partials_kernel<<<(unsigned)((mn + THREADS - 1) / THREADS), THREADS, 0, s>>>(
         m, n, used, part, C, ldc);
@@ -695,16 +778,15 @@ size_t gemm_f64_split_bytes(int m, int n, int k) {
 hipError_t launch_gemm_f64_split(int trans_a, int trans_b, int m, int n, int k, const double *A,
                                  int64_t lda, const double *B, int64_t ldb, double *C,
                                  int64_t ldc, double *part, hipStream_t s) {
-    const int parts = split_parts(m, n, k);
-    if (parts == 0 || part == nullptr)
+    if (split_room(m, n, k) == 0 || part == nullptr)
         return launch_gemm_f64(trans_a, trans_b, m, n, k, A, lda, B, ldb, C, ldc, s);
     if (!trans_a && !trans_b)
-        return launch_split<true, false>(m, n, k, A, lda, B, ldb, C, ldc, part, parts, s);
+        return launch_split<true, false>(m, n, k, A, lda, B, ldb, C, ldc, part, s);
     if (!trans_a && trans_b)
-        return launch_split<true, true>(m, n, k, A, lda, B, ldb, C, ldc, part, parts, s);
+        return launch_split<true, true>(m, n, k, A, lda, B, ldb, C, ldc, part, s);
     if (trans_a && !trans_b)
-        return launch_split<false, false>(m, n, k, A, lda, B, ldb, C, ldc, part, parts, s);
-    return launch_split<false, true>(m, n, k, A, lda, B, ldb, C, ldc, part, parts, s);
+        return launch_split<false, false>(m, n, k, A, lda, B, ldb, C, ldc, part, s);
+    return launch_split<false, true>(m, n, k, A, lda, B, ldb, C, ldc, part, s);
 }
 
 int gemm_f64_row_cut(int m, int n, int k) {

@@ -27,7 +27,8 @@ def chunk(m, n, k):
 @pytest.mark.parametrize("m,n,k", [
     (1024, 1024, 1024), (1024, 1024, 2048), (1024, 1024, 8192), (1408, 1408, 4096),
     (512, 512, 16384), (300, 500, 20032), (1024, 128, 65536), (768, 768, 8192), (64, 64, 4096),
-    (100, 1500, 3008), (33, 47, 1344), (1000, 1001, 1088),
+    (100, 1500, 3008), (33, 47, 1344), (1000, 1001, 1088), (1024, 1024, 2063), (700, 900, 1030),
+    (200, 200, 20015),
 ])
 @pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)])
 def test_chains_are_no_longer_than_a_chunk(m, n, k, ta, tb):
