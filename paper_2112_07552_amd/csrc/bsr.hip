@@ -325,7 +325,11 @@ __device__ inline bool shares_at(unsigned m, int at, const unsigned *ym) {
     return at >= 0 && (ym == nullptr || (m & ym[at]) != 0u);
 }
 
-__global__ void __launch_bounds__(kThreads)
+// Eight waves per SIMD, which the pairs' loads need in flight (66 registers leave
+// seven, and the eighth share of a launch a round of its own): 2^20 records each,
+// 16384 x 16384 x 1024, 26.1 ms with seven and 23.7 with eight; 4096^3 with 2^18
+// 9.6 and 8.8.
+__global__ void __launch_bounds__(kThreads, 8)
 bsr_product_kernel(int M, int N, int nt, const long long *__restrict__ xkeys,
                    const int *__restrict__ xptr, const double *__restrict__ xt,
                    const long long *__restrict__ ykeys, const int *__restrict__ yptr,
