@@ -584,11 +584,17 @@ hipError_t build_by_bits(const tcu_relation &A, const tcu_relation &B, int M, in
     constexpr unsigned kRows = kThreads / 64;
     const unsigned ra = ((unsigned)p.a.rows + kRows - 1) / kRows;
     const unsigned rb = ((unsigned)p.b.rows + kRows - 1) / kRows;
-    if (ga + gb > 0) tile_bits_kernel<<<ga + gb, kThreads, 0, s>>>(p, ga, st);
+    // both sides' records in one launch, where that may have so many
+    const bool one = (int64_t)ga + gb <= max_workgroups(kThreads);
+    if (one && ga + gb > 0) tile_bits_kernel<<<ga + gb, kThreads, 0, s>>>(p, ga, st);
+    if (!one) tile_bits_kernel<<<ga, kThreads, 0, s>>>(p, ga, st);
+    if (!one) tile_bits_kernel<<<gb, kThreads, 0, s>>>(p, 0u, st);
     tile_count_kernel<<<ra + rb, kThreads, 0, s>>>(p, ra);
     tile_scan_kernel<<<2, kScanThreads, 0, s>>>(p);
     tile_list_kernel<<<ra + rb, kThreads, 0, s>>>(p, ra);
-    if (ga + gb > 0) tile_place_kernel<<<ga + gb, kThreads, 0, s>>>(p, ga);
+    if (one && ga + gb > 0) tile_place_kernel<<<ga + gb, kThreads, 0, s>>>(p, ga);
+    if (!one) tile_place_kernel<<<ga, kThreads, 0, s>>>(p, ga);
+    if (!one) tile_place_kernel<<<gb, kThreads, 0, s>>>(p, 0u);
     return hipGetLastError();
 }
 

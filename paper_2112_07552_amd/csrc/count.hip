@@ -177,10 +177,19 @@ hipError_t launch_count(const tcu_relation &A, const tcu_relation &B, int M, int
     if (e == hipSuccess) e = launch_zero_f64(reinterpret_cast<double *>(qb), bb / 8, s);
     if (e != hipSuccess) return e;
     const int alp = (int)count_lines_pad(M), blp = (int)count_lines_pad(N);
-    const int64_t n = A.n + B.n;
-    if (n > 0)
-        count_planes_kernel<<<(unsigned)((n + kThreads - 1) / kThreads), kThreads, 0, s>>>(
-            A.n, A.group, A.key, B.n, B.group, B.key, M, N, K, qa, alp, qb, blp, st);
+    auto place = [&](int64_t na, int64_t nb) {
+        if (na + nb > 0)
+            count_planes_kernel<<<(unsigned)((na + nb + kThreads - 1) / kThreads), kThreads, 0,
+                                  s>>>(na, A.group, A.key, nb, B.group, B.key, M, N, K, qa, alp,
+                                       qb, blp, st);
+    };
+    if (A.n + B.n <= max_workgroups(kThreads) * kThreads) {
+        place(A.n, B.n);
+    } else {  // too many records for one launch
+        place(A.n, 0);
+        place(0, B.n);
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     return launch_count_planes_product(M, K, N, qa, qb, C, cnt, s);
 }
 

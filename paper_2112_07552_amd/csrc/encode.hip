@@ -512,8 +512,13 @@ hipError_t launch_encode_pair(const tcu_relation &A, const tcu_relation &B, int 
                      (A.flags & TCU_REL_UNIQUE_CELLS) != 0, M, K, X};
     const PairSide b{B.n, B.key, B.group, B.val, B.dtype == TCU_F32,
                      (B.flags & TCU_REL_UNIQUE_CELLS) != 0, K, N, Y};
-    const unsigned ga = grid_for(A.n);
-    encode_pair_kernel<<<ga + grid_for(B.n), kThreads, 0, s>>>(a, b, ga, st);
+    const unsigned ga = grid_for(A.n), gb = grid_for(B.n);
+    if ((int64_t)ga + gb <= max_workgroups(kThreads)) {
+        encode_pair_kernel<<<ga + gb, kThreads, 0, s>>>(a, b, ga, st);
+    } else {  // too many records for one launch
+        if (ga > 0) encode_pair_kernel<<<ga, kThreads, 0, s>>>(a, b, ga, st);
+        if (gb > 0) encode_pair_kernel<<<gb, kThreads, 0, s>>>(a, b, 0u, st);
+    }
     return hipGetLastError();
 }
 

@@ -44,6 +44,10 @@ constexpr size_t kAlign = 256;
 
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
+// Workgroups a launch may have along one dimension of the grid: its work-items
+// are counted in 32 bits.
+constexpr int64_t max_workgroups(int threads) { return 0xffffffffLL / threads; }
+
 // Launch records of the matrix-core product kernels (tcu_trace_launches):
 // the calling thread's buffer, or none.  A TraceScope around one launch
 // records the begin event before it and the end event after it, on the
