@@ -571,8 +571,7 @@ double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus, int parts 
         which == kTile         ? Shape{BM, BN, 2, 0.84, 0.94, 8.0}
         : which == kDirectWide ? Shape{32, 64, 2, nt ? 0.62 : 0.65, nt ? 0.62 : 0.80, 6.0}
                                : Shape{32, 32, 4, 0.50, nt ? 0.50 : 0.68, 4.0};
-    const double tiles =
-        (double)((m + sh.bm - 1) / sh.bm) * ((n + sh.bn - 1) / sh.bn) * parts;
+    const double tiles = ceil((double)m / sh.bm) * ceil((double)n / sh.bn) * parts;
     const double one_us = 2.0 * sh.bm * sh.bn * (double)k / 0.307e6;
     const double rounds = floor(tiles / (sh.per_cu * cus));
     const double left = tiles - rounds * sh.per_cu * cus;
@@ -613,14 +612,27 @@ void launch_direct(int m, int n, int k, const double *A, int64_t lda, const doub
                    int64_t ldb, double *C, int64_t ldc, int accumulate, int kc, int parts,
                    int stages, const uint32_t *only_if, hipStream_t s) {
     const int64_t cstride = (int64_t)m * n;
-    const dim3 grid((unsigned)(((m + 16 * TM - 1) / (16 * TM)) * ((n + 16 * TN - 1) / (16 * TN))),
-                    (unsigned)parts);
-    if (offsets_fit(A_KC, std::min(m, 16 * TM), lda) && offsets_fit(B_KC, std::min(n, 16 * TN), ldb))
-        gemm_direct_kernel<A_KC, B_KC, TM, TN, false><<<grid, THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, stages, only_if);
-    else
-        gemm_direct_kernel<A_KC, B_KC, TM, TN, true><<<grid, THREADS, 0, s>>>(
-            m, n, k, A, lda, B, ldb, C, ldc, accumulate, kc, cstride, stages, only_if);
+    const bool narrow = offsets_fit(A_KC, std::min(m, 16 * TM), lda) &&
+                        offsets_fit(B_KC, std::min(n, 16 * TN), ldb);
+    auto *kernel = narrow ? gemm_direct_kernel<A_KC, B_KC, TM, TN, false>
+                          : gemm_direct_kernel<A_KC, B_KC, TM, TN, true>;
+    // as many tiles per launch as it may have workgroups (a C of 2^29 cells and
+    // more in a line, or of 137 GB, takes several)
+    const int64_t down = ((int64_t)m + 16 * TM - 1) / (16 * TM);
+    const int64_t across = ((int64_t)n + 16 * TN - 1) / (16 * TN);
+    const int64_t most = max_workgroups(THREADS);
+    const int64_t step_n = std::min(across, most), step_m = std::min(down, most / step_n);
+    for (int64_t tm = 0; tm < down; tm += step_m)
+        for (int64_t tn = 0; tn < across; tn += step_n) {
+            const int64_t r0 = tm * 16 * TM, c0 = tn * 16 * TN;
+            const int mm = (int)std::min<int64_t>(m - r0, step_m * 16 * TM);
+            const int nn = (int)std::min<int64_t>(n - c0, step_n * 16 * TN);
+            const dim3 grid((unsigned)(std::min(down - tm, step_m) * std::min(across - tn, step_n)),
+                            (unsigned)parts);
+            kernel<<<grid, THREADS, 0, s>>>(mm, nn, k, A + (A_KC ? r0 * lda : r0), lda,
+                                            B + (B_KC ? c0 * ldb : c0), ldb, C + r0 * ldc + c0,
+                                            ldc, accumulate, kc, cstride, stages, only_if);
+        }
 }
 
 // The product on kernel `which`; parts > 1: in chunks of kc of k, their partial

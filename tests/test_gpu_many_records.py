@@ -1,7 +1,8 @@
 """Relations of so many records that both together exceed the 2^32 work-items
 of one launch, while each alone does not.  Every record falls on one cell and
 carries the same value, so declared unique (plain stores) the cell holds that
-value; the columns of both relations share one tensor."""
+value; the columns of both relations share one tensor.  And products with so
+many tiles."""
 import pytest
 import torch
 
@@ -43,3 +44,18 @@ def test_block_sparse():
     want = torch.zeros((20, 40), dtype=torch.float64, device=g.device)
     want[0, 0] = 9.0
     assert torch.equal(C, want)
+
+
+@pytest.mark.parametrize("ta,tb", [(False, False), (False, True), (True, False)])
+@pytest.mark.parametrize("m,n", [((1 << 29) + 33, 3), (3, (1 << 29) + 33)])
+def test_product_with_a_line_of_cells(m, n, ta, tb):
+    """32 x 32 tiles of one line of 2^29 cells and more: as many workgroups of
+    256 as 2^32 work-items and beyond."""
+    dev = cuda_or_skip()
+    if torch.cuda.mem_get_info(dev)[0] < 32 << 30:
+        pytest.skip("not enough GPU memory")
+    A = torch.full((2, m) if ta else (m, 2), 3.0, dtype=torch.float64, device=dev)
+    B = torch.full((n, 2) if tb else (2, n), 5.0, dtype=torch.float64, device=dev)
+    out = torch.zeros((m, n), dtype=torch.float64, device=dev)
+    ops.gemm_f64(A, B, trans_a=ta, trans_b=tb, out=out)
+    assert float(out.min()) == 30.0 and float(out.max()) == 30.0
