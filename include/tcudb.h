@@ -403,10 +403,14 @@ tcu_status tcu_mfma_peak(int kind, int32_t iters, void *out, hipStream_t stream)
  * signed 64-bit).  codes_a[i] = the rank of a[i] in that list (0-based), and
  * likewise codes_b; dict (capacity n_a + n_b) receives v_1..v_k and *k (a
  * host pointer) receives k.  Codes are independent of record order.  The
- * call SYNCHRONISES the stream once (for *k; the sort of more than 1024
- * distinct values and their codes are enqueued after that).  n_a + n_b must not exceed 2^31 - 1.  ws: at least
- * tcu_dict_workspace_bytes(n_a + n_b) bytes, 256-byte aligned (about 24
- * bytes per value); errors are returned, not recorded in ws. */
+ * call SYNCHRONISES the stream for *k (the sort of more than 1024 distinct
+ * values and their codes are enqueued after that): once for up to 2^17 values
+ * or distinct values, and once more for each larger hash table that is tried
+ * after that, at most three times in all (more than 2^17 distinct values
+ * twice, more than 2^20 three times; fewer too where 64 or more of them fall on
+ * neighbouring slots).  n_a + n_b must not exceed 2^31 - 1.  ws: at least
+ * tcu_dict_workspace_bytes(n_a + n_b) bytes, 256-byte aligned (about 24 bytes
+ * per value); errors are returned, not recorded in ws. */
 size_t tcu_dict_workspace_bytes(int64_t n);
 tcu_status tcu_dict_encode(const int64_t *a, int64_t n_a, const int64_t *b, int64_t n_b,
                            int32_t *codes_a, int32_t *codes_b, int64_t *dict, int64_t *k,
@@ -445,9 +449,9 @@ tcu_status tcu_join_agg_row(const tcu_relation *A, const tcu_relation *B, int32_
  *    joins).  With A->val == NULL and B->val == NULL, C is the pair count.
  * Cost: asynchronous while a bit per tile of both grids takes at most 64 MiB (and
  *    each has at most 65536 tiles along M or N);
- *    beyond that, building the tiles makes ONE host synchronisation per
- *    relation (for the number of its distinct tile keys), and the call blocks
- *    until the stream has reached that point.
+ *    beyond that, building the tiles makes one to three host synchronisations
+ *    per relation (tcu_dict_encode's, for the number of its distinct tile
+ *    keys), and the call blocks until the stream has reached that point.
  * Records out of range are skipped and counted (tcu_sync_status).
  * Duplicate cells add up (FP64 atomics) unless TCU_REL_UNIQUE_CELLS is set.
  * Workspace: tcu_join_agg_bsr_workspace_bytes(); it bounds the tile storage

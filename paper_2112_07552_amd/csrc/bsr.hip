@@ -24,7 +24,8 @@
 //
 // No step needs the host.  Where the bits would take more memory than the
 // dictionary machinery (kMaxBitBytes), steps 1-3 take the distinct tile keys
-// (outer << 32 | key tile) and their ranks from that, one host wait per side.
+// (outer << 32 | key tile) and their ranks from that, one to three host waits per
+// side.
 #include <algorithm>
 
 #include "internal.h"
