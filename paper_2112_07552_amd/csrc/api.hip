@@ -688,11 +688,15 @@ size_t tcu_workspace_bytes(const tcu_relation *A, const tcu_relation *B, int32_t
                            int32_t N, tcu_precision p, int flags) {
     if (!shapes_ok(M, K, N)) return 0;
     if (!precision_ok(p)) return 0;
-    return plan_layout(M, K, N, p, flags, count_planes(A, B, flags)).total +
-           std::max(enc_scratch_bytes(A, B, M, K, N),
-                    (flags & TCU_WS_SCRATCH) != 0
-                        ? bin_scratch_bytes(A, B, M, K, N, p, (flags & TCU_WS_COUNT) != 0)
-                        : 0);
+    const bool planes = count_planes(A, B, flags);
+    const size_t bytes =
+        plan_layout(M, K, N, p, flags, planes).total + enc_scratch_bytes(A, B, M, K, N);
+    if ((flags & TCU_WS_SCRATCH) == 0) return bytes;
+    // the forward's scratch starts where the forward's layout ends: the
+    // backward's buffers serve it too
+    const size_t bin = bin_scratch_bytes(A, B, M, K, N, p, (flags & TCU_WS_COUNT) != 0);
+    return std::max(bytes,
+                    plan_layout(M, K, N, p, flags & ~TCU_WS_BACKWARD, planes).total + bin);
 }
 
 int tcu_mixed_plan(tcu_precision p, int32_t k, double tol, uint32_t need, double u,
