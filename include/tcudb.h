@@ -145,10 +145,11 @@ typedef struct {
  * 3.3 encodings X and Y, plus the status block; with TCU_WS_BACKWARD the two
  * gradient matrices; in the mixed forms the certificate's planes, digit
  * slices or residues; in the FP64 form, for products with too few output
- * tiles to fill the chip, the partial products of their split contraction).  Given the relations (A and B not NULL), the size also
- * holds the scratch with which an encoding of 1 GiB or more runs window by
- * window (tcu_encode); a workspace sized without it (A or B NULL) is still
- * accepted and encodes in one pass.  The workspace must be 256-byte aligned.
+ * tiles to fill the chip, the partial products of their split contraction).
+ * Given the relations (A and B not NULL), the size also holds the scratch with
+ * which an encoding of 1 GiB or more runs window by window (tcu_encode); a
+ * workspace sized without it (A or B NULL) is still accepted and encodes in one
+ * pass.  The workspace must be 256-byte aligned.
  * Returns 0 for invalid shapes. */
 size_t tcu_workspace_bytes(const tcu_relation *A, const tcu_relation *B, int32_t M, int32_t K,
                            int32_t N, tcu_precision p, int flags);

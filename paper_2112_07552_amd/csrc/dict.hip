@@ -390,10 +390,11 @@ dict_rank_kernel(const long long *__restrict__ sorted, Table t, const DictState 
     if (s >= 0) t.code[s] = (int)(r + shift);
 }
 
-// Codes of both columns, if the dictionary has at most `limit` values.  A dictionary of at most kLdsDict values is put into
-// an LDS hash table by each workgroup when the columns are long enough to
-// repay it (kLdsMinN): 2^24 records with 32 distinct values 38 us (5.3 TB/s)
-// against 72 us through the table in memory.
+// Codes of both columns, if the dictionary has at most `limit` values.  A
+// dictionary of at most kLdsDict values is put into an LDS hash table by each
+// workgroup when the columns are long enough to repay it (kLdsMinN): 2^24 records
+// with 32 distinct values 38 us (5.3 TB/s) against 72 us through the table in
+// memory.
 constexpr int kLookThreads = 512;
 constexpr int kLdsDict = 2048;
 constexpr int kLdsBits = 12;

@@ -84,9 +84,9 @@ __device__ inline T column(const T *p, int64_t i) {
 // records are read past the caches, which the matrix needs (past_caches): 2^24
 // records into 134 MB 239 us, 225 so.  Smaller columns may still be cached from
 // the kernel that wrote them, and the pair kernel reads them through the caches:
-// 2^20 records 85 us for the whole forward, 92 past them.  The random stores bound it (75 G
-// records/s; 85 where one XCD stores to 512 KB at a time, so neither memory nor
-// the fabric does).
+// 2^20 records 85 us for the whole forward, 92 past them.  The random stores
+// bound it (75 G records/s; 85 where one XCD stores to 512 KB at a time, so
+// neither memory nor the fabric does).
 template <typename T, bool UNIQUE, bool PAST>
 __global__ void __launch_bounds__(kThreads)
 encode_kernel(int64_t n, const int32_t *__restrict__ grp, const int32_t *__restrict__ key,

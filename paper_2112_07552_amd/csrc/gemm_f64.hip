@@ -37,6 +37,10 @@
 //  * Products whose output has too few 128 x 128 tiles to fill the chip, or
 //    edges that waste much of one, run on the direct kernel (below), whose
 //    tiles are an eighth or a sixteenth of that; pick_kernel holds the rule.
+//  * Where such an output's contraction is long it is split into chunks over
+//    workgroups, on either kernel, and the partial products are added up in
+//    chunk order; pick_split holds the rule.  No chain of additions is longer
+//    than a chunk of the 128 x 128 tiles' split.
 #include <math.h>
 
 #include <algorithm>
@@ -82,9 +86,10 @@ __device__ __forceinline__ double read_frag(const double *__restrict__ L, int wb
 
 // ----- tile path: no vector-ALU work in the main loop.  While the matrix
 // cores are busy, VALU instructions of every wave on the SIMD get few issue
-// slots, so the loop keeps its address arithmetic scalar: each panel load is a uniform SGPR base (advanced by scalar arithmetic) plus
-// the lane's fixed 32-bit byte offset, and the loop is unrolled over the two
-// LDS buffers so every LDS access is a fixed register plus an immediate.
+// slots, so the loop keeps its address arithmetic scalar: each panel load is a
+// uniform SGPR base (advanced by scalar arithmetic) plus the lane's fixed 32-bit
+// byte offset, and the loop is unrolled over the two LDS buffers so every LDS
+// access is a fixed register plus an immediate.
 
 typedef __attribute__((address_space(1))) const char gchar;
 // 16-byte loads at 8-byte alignment (global memory takes them): leading
@@ -384,10 +389,10 @@ __device__ __forceinline__ void fold_run(d4 (&acc)[TM][TN], double *run, bool fi
 }
 
 // The stages 0 .. S - 1 of 16 k, S >= 1, of `total` (one more where a remainder
-// of k follows them).  An accumulator takes at most `stages`
-// of them before its run is folded away: the error of a sum grows with the length
-// of its chain of additions, and where these kernels stand in for the split
-// contraction of 128 x 128 tiles, runs are no longer than its chunks. Relative
+// of k follows them).  An accumulator takes at most `stages` of them before its
+// run is folded away: the error of a sum grows with the length of its chain of
+// additions, and where these kernels stand in for the split contraction of 128 x
+// 128 tiles, runs are no longer than its chunks (kOneRun elsewhere).  Relative
 // RMS error of uniform values with that split, with one chain per wave, and with
 // runs: 1024 x 1024 x 4096 2.3e-16, 4.1e-16 and 2.0e-16; 1408 x 1408 x 8192
 // 5.0e-16, 5.8e-16 and 3.0e-16.  A fold takes about 1% of a run of 256 terms on
@@ -397,7 +402,8 @@ __device__ __forceinline__ void fold_run(d4 (&acc)[TM][TN], double *run, bool fi
 template <bool A_KC, bool B_KC, int TM, int TN, bool EDGE, bool WIDE>
 __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa,
                                               const DirectOp<B_KC, TN, WIDE> &ob, int S,
-                                              int total, int stages, d4 (&acc)[TM][TN], double *run) {
+                                              int total, int stages, d4 (&acc)[TM][TN],
+                                              double *run) {
     constexpr int NB = TM * TN > 4 ? 3 : 2;  // stages in registers
     constexpr int IA = direct_items<A_KC, TM, EDGE>(), IB = direct_items<B_KC, TN, EDGE>();
     constexpr int MF = 4 * TM * TN;
@@ -508,9 +514,11 @@ gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t ld
     bool folded = false;
     if (S > 0) {
         if ((A_KC || m0 + TILE_M <= m) && (B_KC || n0 + TILE_N <= n))
-            folded = direct_stages<A_KC, B_KC, TM, TN, false, WIDE>(oa, ob, S, total, stages, acc, run);
+            folded = direct_stages<A_KC, B_KC, TM, TN, false, WIDE>(oa, ob, S, total, stages, acc,
+                                                                    run);
         else
-            folded = direct_stages<A_KC, B_KC, TM, TN, true, WIDE>(oa, ob, S, total, stages, acc, run);
+            folded = direct_stages<A_KC, B_KC, TM, TN, true, WIDE>(oa, ob, S, total, stages, acc,
+                                                                   run);
     }
     if (left > 0) {
         double fa[TM][4], fb[TN][4];

@@ -173,18 +173,18 @@ int split_chunk_steps(int S, int digit_bf16);
 hipError_t launch_gemm_f64(int trans_a, int trans_b, int m, int n, int k, const double *A,
                            int64_t lda, const double *B, int64_t ldb, double *C, int64_t ldc,
                            hipStream_t s, int accumulate = 0, const uint32_t *only_if = nullptr);
-// The same product with the contraction split into chunks whose partial
-// products go to `part` and are summed in chunk order, when the output has
-// too few tiles to fill the chip (gemm_f64_split_bytes > 0); otherwise (or
+// The same product, its contraction split into chunks whose partial products
+// go to `part` and are summed in chunk order where that is faster, for outputs
+// with too few tiles to fill the chip (gemm_f64_split_bytes > 0); otherwise (or
 // part == NULL) launch_gemm_f64.  part: gemm_f64_split_bytes(m, n, k) bytes.
 size_t gemm_f64_split_bytes(int m, int n, int k);
 hipError_t launch_gemm_f64_split(int trans_a, int trans_b, int m, int n, int k, const double *A,
                                  int64_t lda, const double *B, int64_t ldb, double *C,
                                  int64_t ldc, double *part, hipStream_t s);
 // Rows m1 (a multiple of the tile height, 0 < m1 < m) at which an m x n FP64
-// product A^T B (contraction k, dense operands) can be cut into two launches that together take no more rounds of
-// concurrently resident workgroups than one launch; 0 when no such cut exists
-// or the product fills at most one round.
+// product A^T B (contraction k, dense operands) can be cut into two launches
+// that together take no more rounds of concurrently resident workgroups than one
+// launch; 0 when no such cut exists or the product fills at most one round.
 int gemm_f64_row_cut(int m, int n, int k);
 
 // count.hip: the product of two 0/1 encodings (relations with unique cells,

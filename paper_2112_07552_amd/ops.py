@@ -325,7 +325,9 @@ def join_agg_row(a_key, a_val, b_key, b_group, b_val, K: int, N: int, with_count
 def join_agg_bsr(a_group, a_key, a_val, b_key, b_group, b_val, M: int, K: int, N: int,
                  unique: bool = False) -> Tuple[torch.Tensor, torch.Tensor]:
     """The operator on 16 x 16 block-sparse encodings (Section 4.2.4):
-    returns (C [M, N] FP64, workspace).  Blocks once per relation."""
+    returns (C [M, N] FP64, workspace).  Blocks only where a bit per 16 x 16
+    tile of both grids takes more than 64 MiB (or one has more than 65536 tiles
+    along M or N)."""
     A = make_relation(a_group, a_key, a_val, unique)
     B = make_relation(b_group, b_key, b_val, unique)
     dev = a_group.device
