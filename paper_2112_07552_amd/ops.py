@@ -224,8 +224,7 @@ def join_agg_fwd(a_group, a_key, a_val, b_key, b_group, b_val, M: int, K: int, N
     B = make_relation(b_group, b_key, b_val, unique)
     dev = a_group.device
     flags = dict(count=with_count, backward=for_backward)
-    need = workspace_bytes(A, B, M, K, N, precision, **flags)
-    own = ws is None or ws.numel() < need
+    own = ws is None or ws.numel() < workspace_bytes(A, B, M, K, N, precision, **flags)
     if own:
         ws = alloc_workspace(workspace_bytes(A, B, M, K, N, precision, scratch=True, **flags), dev)
     Cm = torch.empty((M, N), dtype=torch.float64, device=dev)
@@ -233,11 +232,13 @@ def join_agg_fwd(a_group, a_key, a_val, b_key, b_group, b_val, M: int, K: int, N
     check(_lib.load().tcu_join_agg_fwd(C.byref(A), C.byref(B), M, K, N, PRECISIONS[precision],
                                        tol, _ptr(Cm), _ptr(cnt), _ptr(ws), ws.numel(),
                                        _stream(dev)), "tcu_join_agg_fwd")
-    if own and for_backward and ws.numel() > need:
-        # what the backward reads leads the workspace: status block, X and Y
-        kept = 256 + _pad(8 * M * K, 256) + _pad(8 * K * N, 256)
-        scratch, ws = ws, alloc_workspace(need, dev)
-        ws[:kept].copy_(scratch[:kept])
+    if own and for_backward:
+        need = workspace_bytes(A, B, M, K, N, precision, **flags)
+        if ws.numel() > need:
+            # what the backward reads leads the workspace: status block, X and Y
+            kept = 256 + _pad(8 * M * K, 256) + _pad(8 * K * N, 256)
+            scratch, ws = ws, alloc_workspace(need, dev)
+            ws[:kept].copy_(scratch[:kept])
     return Cm, cnt, ws
 
 
