@@ -398,8 +398,9 @@ __device__ __forceinline__ void fold_run(d4 (&acc)[TM][TN], double *run, bool fi
 // 5.0e-16, 5.8e-16 and 3.0e-16.  A fold takes about 1% of a run of 256 terms on
 // the 32 x 32 tiles and 2% on the 32 x 64 ones (1024 x 1024 x 2048, two folds: 67.4
 // and 70.7 us).
-// Returns whether a run has been folded.
-template <bool A_KC, bool B_KC, int TM, int TN, bool EDGE, bool WIDE>
+// Returns whether a run has been folded.  RUNS: a wave has more stages than one
+// run takes; without the folds' code 1024^3 takes 37.4 us, with it 38.1.
+template <bool A_KC, bool B_KC, int TM, int TN, bool EDGE, bool WIDE, bool RUNS>
 __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa,
                                               const DirectOp<B_KC, TN, WIDE> &ob, int S,
                                               int total, int stages, d4 (&acc)[TM][TN],
@@ -420,9 +421,11 @@ __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa
         for (int i = 0; i < IB; ++i) direct_load<B_KC, TN, EDGE, WIDE>(ob, bb, i, fb[u]);
     }
     // runs of equal length, in whole rounds of NB stages
-    const int runs = (total + stages - 1) / stages;
-    const int fold = min((total + runs * NB - 1) / (runs * NB), stages / NB) * NB;
-    int next = fold;
+    int fold = 0, next = 0;
+    if constexpr (RUNS) {
+        const int runs = (total + stages - 1) / stages;
+        fold = next = min((total + runs * NB - 1) / (runs * NB), stages / NB) * NB;
+    }
     for (int s = 0; s < S; s += NB) {
 #pragma unroll
         for (int u = 0; u < NB; ++u) {
@@ -448,10 +451,11 @@ __device__ __forceinline__ bool direct_stages(const DirectOp<A_KC, TM, WIDE> &oa
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
-        if (s + NB == next && total - next > stages - fold) {
-            fold_run<TM, TN>(acc, run, next == fold);
-            next += fold;
-        }
+        if constexpr (RUNS)
+            if (s + NB == next && total - next > stages - fold) {
+                fold_run<TM, TN>(acc, run, next == fold);
+                next += fold;
+            }
     }
     return next > fold;
 }
@@ -474,8 +478,9 @@ __device__ __forceinline__ void direct_tail(const DirectOp<KC, F, WIDE> &o, int 
         }
 }
 
-// kc > 0: split contraction, as gemm_f64_kernel.  stages: of a run (direct_stages), at least 16.
-template <bool A_KC, bool B_KC, int TM, int TN, bool WIDE>
+// kc > 0: split contraction, as gemm_f64_kernel.  stages: of a run, at least 16;
+// RUNS: a wave has more (direct_stages).
+template <bool A_KC, bool B_KC, int TM, int TN, bool WIDE, bool RUNS>
 __global__ void __launch_bounds__(THREADS)
 gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t lda,
                    const double *__restrict__ B, int64_t ldb, double *__restrict__ C,
@@ -514,11 +519,11 @@ gemm_direct_kernel(int m, int n, int k, const double *__restrict__ A, int64_t ld
     bool folded = false;
     if (S > 0) {
         if ((A_KC || m0 + TILE_M <= m) && (B_KC || n0 + TILE_N <= n))
-            folded = direct_stages<A_KC, B_KC, TM, TN, false, WIDE>(oa, ob, S, total, stages, acc,
-                                                                    run);
+            folded = direct_stages<A_KC, B_KC, TM, TN, false, WIDE, RUNS>(oa, ob, S, total, stages,
+                                                                          acc, run);
         else
-            folded = direct_stages<A_KC, B_KC, TM, TN, true, WIDE>(oa, ob, S, total, stages, acc,
-                                                                   run);
+            folded = direct_stages<A_KC, B_KC, TM, TN, true, WIDE, RUNS>(oa, ob, S, total, stages,
+                                                                         acc, run);
     }
     if (left > 0) {
         double fa[TM][4], fb[TN][4];
@@ -622,8 +627,13 @@ void launch_direct(int m, int n, int k, const double *A, int64_t lda, const doub
     const int64_t cstride = (int64_t)m * n;
     const bool narrow = offsets_fit(A_KC, std::min(m, 16 * TM), lda) &&
                         offsets_fit(B_KC, std::min(n, 16 * TN), ldb);
-    auto *kernel = narrow ? gemm_direct_kernel<A_KC, B_KC, TM, TN, false>
-                          : gemm_direct_kernel<A_KC, B_KC, TM, TN, true>;
+    // stages of a wave's share of the contraction
+    constexpr int per_wave = THREADS / 64 * BK;
+    const bool runs = ((int64_t)(kc > 0 ? kc : k) + per_wave - 1) / per_wave > stages;
+    auto *kernel = narrow ? (runs ? gemm_direct_kernel<A_KC, B_KC, TM, TN, false, true>
+                                  : gemm_direct_kernel<A_KC, B_KC, TM, TN, false, false>)
+                          : (runs ? gemm_direct_kernel<A_KC, B_KC, TM, TN, true, true>
+                                  : gemm_direct_kernel<A_KC, B_KC, TM, TN, true, false>);
     // as many tiles per launch as it may have workgroups (a C of 2^29 cells and
     // more in a line, or of 137 GB, takes several)
     const int64_t down = ((int64_t)m + 16 * TM - 1) / (16 * TM);
