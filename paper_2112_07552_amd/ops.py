@@ -232,7 +232,7 @@ def join_agg_fwd(a_group, a_key, a_val, b_key, b_group, b_val, M: int, K: int, N
     check(_lib.load().tcu_join_agg_fwd(C.byref(A), C.byref(B), M, K, N, PRECISIONS[precision],
                                        tol, _ptr(Cm), _ptr(cnt), _ptr(ws), ws.numel(),
                                        _stream(dev)), "tcu_join_agg_fwd")
-    if own and for_backward:
+    if own and for_backward and not unique:  # unique cells take no scratch
         need = workspace_bytes(A, B, M, K, N, precision, **flags)
         if ws.numel() > need:
             # what the backward reads leads the workspace: status block, X and Y
