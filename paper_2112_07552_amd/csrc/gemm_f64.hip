@@ -395,9 +395,10 @@ __device__ __forceinline__ void fold_run(d4 (&acc)[TM][TN], double *run, bool fi
 // 128 tiles, runs are no longer than its chunks (kOneRun elsewhere).  Relative
 // RMS error of uniform values with that split, with one chain per wave, and with
 // runs: 1024 x 1024 x 4096 2.3e-16, 4.1e-16 and 2.0e-16; 1408 x 1408 x 8192
-// 5.0e-16, 5.8e-16 and 3.0e-16.  A fold takes about 1% of a run of 256 terms on
-// the 32 x 32 tiles and 2% on the 32 x 64 ones (1024 x 1024 x 2048, two folds: 67.4
-// and 70.7 us).
+// 5.0e-16, 5.8e-16 and 3.0e-16.  A fold costs 1 to 2 us of LDS traffic,
+// which all waves have at the same time (1024 x 1024 x 2048, two folds: 67.5 and
+// 71.2 us; x 4096 127.1 and 130.7); with the folds between two loops over stages
+// instead of in one it took the same.
 // Returns whether a run has been folded.  RUNS: a wave has more stages than one
 // run takes; without the folds' code 1024^3 takes 37.4 us, with it 38.1.
 template <bool A_KC, bool B_KC, int TM, int TN, bool EDGE, bool WIDE, bool RUNS>
@@ -572,19 +573,24 @@ enum Kernel { kTile, kDirectWide, kDirectSmall };  // 128 x 128; 32 x 64; 32 x 3
 // 8.4; 1024^3 126, 43, 45; 2048^3 278, 306, 332; 4096^3 1867, 1998, -; 1500 x
 // 2777 x 2051 (264 tiles) 478, 336, 342; 3000^3 1030, 846, -.  The direct kernels
 // read both operands of A B^T in 64-byte pieces of many rows, which costs them
-// more (2048^3: 368, the tile kernel 265; 1024 x 1024 x 8192 365 and 266 TN, 512 x
-// 512 x 16384 226 and 143).
-// parts: that many such products, of k each, in one launch.
-double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus, int parts = 1) {
+// more (2048^3: 368, the tile kernel 265), and more yet where few tiles of a long
+// contraction leave the reads their latency (1024 x 1024 x 8192 365 and 266 TN, 512
+// x 512 x 16384 226 and 143).
+// parts: that many such products, of k each, in one launch; 0: one product, of an
+// output without room for partial products.
+double kernel_us(Kernel which, bool nt, int m, int n, int k, int cus, int parts = 0) {
     struct Shape {
         int bm, bn, per_cu;
         double one, full, fixed;
     };
-    const Shape sh =
+    Shape sh =
         which == kTile         ? Shape{BM, BN, 2, 0.84, 0.94, 8.0}
-        : which == kDirectWide ? Shape{32, 64, 2, nt ? 0.62 : 0.65, nt ? 0.62 : 0.80, 6.0}
-                               : Shape{32, 32, 4, 0.50, nt ? 0.50 : 0.68, 4.0};
-    const double tiles = ceil((double)m / sh.bm) * ceil((double)n / sh.bn) * parts;
+        : which == kDirectWide ? Shape{32, 64, 2, 0.65, nt ? 0.66 : 0.80, 6.0}
+                               : Shape{32, 32, 4, 0.50, nt ? 0.58 : 0.68, 4.0};
+    if (nt && parts > 0 && which == kDirectWide) sh.one = sh.full = 0.62;
+    if (nt && parts > 0 && which == kDirectSmall) sh.full = sh.one;
+    const double tiles =
+        ceil((double)m / sh.bm) * ceil((double)n / sh.bn) * std::max(parts, 1);
     const double one_us = 2.0 * sh.bm * sh.bn * (double)k / 0.307e6;
     const double rounds = floor(tiles / (sh.per_cu * cus));
     const double left = tiles - rounds * sh.per_cu * cus;
@@ -770,7 +776,8 @@ SplitPlan pick_split(bool a_kc, bool b_kc, int m, int n, int k, int64_t lda, int
             consider(kDirectSmall, (w * cus + tiles - 1) / tiles, 0.75);
         }
     }
-    if (tile_ok) consider(kTile, room, 0.93);
+    // (a few tiles' estimate errs more: 300 x 300 x 9000 A B^T 68 us for 88)
+    if (tile_ok) consider(kTile, room, tiles <= 128 ? 0.85 : 0.93);
     return best;
 }
 
